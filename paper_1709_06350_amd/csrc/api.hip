@@ -139,12 +139,9 @@ int Ctx::read_scalars(int slot, int count, double* out) {
   return MR_OK;
 }
 
-int Ctx::write_scalar(int slot, double v) {
-  host[kHostSlots - 1] = v;
-  hipError_t e = hipMemcpyAsync(scal + slot, host + kHostSlots - 1, sizeof(double), hipMemcpyHostToDevice, stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(stream);
-  if (e != hipSuccess) return hip_fail(e, "write scalar");
-  return MR_OK;
+int Ctx::write_scalars(int slot, double v0, double v1, int count) {
+  hipError_t e = launch_set_scalars(scal + slot, v0, v1, count, stream);
+  return e == hipSuccess ? MR_OK : hip_fail(e, "write scalars");
 }
 
 // ---- event timing of finest-mesh sweeps ----------------------------------------------------
@@ -381,17 +378,22 @@ int Ctx::finest_norm(const double* theta_split, ShiftRef sh, double* nrm, double
   return MR_OK;
 }
 
-// Validate delta, convert it to the colour-split layout and build its hierarchy.
-int Ctx::prepare(const double* delta) {
+// Validate delta, convert it to the colour-split layout and build its hierarchy. With nrm0 also the
+// norm and <Sigma> of the residual at theta = 0, and the running sums of the finest level from it.
+int Ctx::prepare(const double* delta, double* nrm0, double* msig0) {
   Level& L0 = lv[0];
-  hipError_t e = launch_validate(delta, L0.cells, reducer(kSlotRes), stream);
-  if (e != hipSuccess) return hip_fail(e, "validate");
-  double bad;
-  int rc = read_scalars(kSlotRes, 1, &bad);
+  hipError_t e = launch_intake(delta, L0.delta, L0.n, nrm0 != nullptr, nrm0 ? lsum(0) : nullptr, reducer(kSlotRes), stream);
+  if (e != hipSuccess) return hip_fail(e, "intake");
+  double v[3];
+  int rc = read_scalars(kSlotRes, 3, v);
   if (rc != MR_OK) return rc;
-  if (bad != 0.0) return fail(MR_EDOMAIN, "delta has %.0f cells with a non-finite value or 1 + delta <= 0", bad);
-  e = launch_to_split(delta, L0.delta, L0.n, stream);
-  if (e != hipSuccess) return hip_fail(e, "to_split");
+  if (v[0] != 0.0) return fail(MR_EDOMAIN, "delta has %.0f cells with a non-finite value or 1 + delta <= 0", v[0]);
+  if (nrm0) {
+    const double N3 = (double)L0.cells;
+    const double var = v[2] - v[1] * v[1] / N3;
+    *nrm0 = std::sqrt(var > 0.0 ? var : 0.0);
+    *msig0 = -v[1] / N3;
+  }
   for (int l = 1; l < nlev; ++l) {
     e = launch_restrict(lv[l - 1].delta, lv[l].delta, lv[l - 1].n, stream);
     if (e != hipSuccess) return hip_fail(e, "restrict delta");
@@ -401,7 +403,8 @@ int Ctx::prepare(const double* delta) {
 
 int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_depth) {
   auto t0 = std::chrono::steady_clock::now();
-  int rc = prepare(delta);
+  double r0, m0, nrm, msig;
+  int rc = prepare(delta, &r0, &m0);   // also the running sums of Sigma at theta = 0
   if (rc != MR_OK) return rc;
   if (aa_depth > 0 && (rc = aa_reserve(aa_depth)) != MR_OK) return rc;
   AAState aa(aa_depth, aa_depth + 1);
@@ -412,18 +415,15 @@ int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_de
   if (opts.warm_start) e = launch_to_split(theta, L0.th[0], L0.n, stream);
   else e = hipMemsetAsync(L0.th[0], 0, L0.cells * sizeof(double), stream);
   if (e != hipSuccess) return hip_fail(e, "initial theta");
-  double r0, m0, nrm, msig;
-  if ((rc = finest_norm(nullptr, ShiftRef{nullptr, 0.0, 0.0}, &r0, &m0)) != MR_OK) return rc;
   if (opts.warm_start) {
     if ((rc = finest_norm(L0.th[0], ShiftRef{nullptr, 0.0, 0.0}, &nrm, &msig)) != MR_OK) return rc;
+    // running sums of the finest level, so that the first sweep uses the exact <Sigma>
+    if ((rc = write_scalars(kSlotLevel, msig * N3, 0.0)) != MR_OK) return rc;
   } else {
     nrm = r0;
     msig = m0;
   }
   if (r0 == 0.0) r0 = 1.0;
-  // Running sums of the finest level, so that the first sweep uses the exact <Sigma>.
-  if ((rc = write_scalar(kSlotLevel + 0, msig * N3)) != MR_OK) return rc;
-  if ((rc = write_scalar(kSlotLevel + 1, 0.0)) != MR_OK) return rc;
   double rel = nrm / r0;
   mr_info loc{};
   loc.r0_norm = r0;
@@ -765,12 +765,14 @@ int mr_residual(mr_ctx* h, const double* delta, const double* theta, double* r_o
   if (!h || !delta || !theta) return fail(MR_EINVAL, "mr_residual: null argument");
   Ctx* c = reinterpret_cast<Ctx*>(h);
   Level& L0 = c->lv[0];
-  hipError_t e = launch_to_split(delta, L0.delta, L0.n, c->stream);
+  hipError_t e = launch_intake(delta, L0.delta, L0.n, true, nullptr, c->reducer(kSlotAux), c->stream);
   if (e == hipSuccess) e = launch_to_split(theta, L0.th[1], L0.n, c->stream);
   if (e != hipSuccess) return hip_fail(e, "mr_residual");
   int rc;
-  double r0, m0, n1, m1;
-  if ((rc = c->finest_norm(nullptr, ShiftRef{nullptr, 0.0, 0.0}, &r0, &m0)) != MR_OK) return rc;
+  double v0[3], n1, m1;   // (., sum b, sum b^2) at theta = 0
+  if ((rc = c->read_scalars(kSlotAux, 3, v0)) != MR_OK) return rc;
+  const double var0 = v0[2] - v0[1] * v0[1] / (double)L0.cells;
+  const double r0 = std::sqrt(var0 > 0.0 ? var0 : 0.0);
   if ((rc = c->finest_norm(L0.th[1], ShiftRef{nullptr, 0.0, 0.0}, &n1, &m1)) != MR_OK) return rc;
   // second pass with the mean of Sigma, writing r in natural order
   e = launch_residual(L0.th[1], L0.delta, L0.n, 1.0, ShiftRef{nullptr, 0.0, m1}, r_out, c->reducer(kSlotRes),

@@ -951,41 +951,33 @@ static int batch_solve(Batch& B, const double* const* delta, double* const* thet
   double* rbuf = B.rbuf;
   hipStream_t cs = B.cs;
   hipError_t e = hipSuccess;
-  // Inputs: validate, convert, delta hierarchy, theta = 0. The residual at theta = 0 gives the
+  // Inputs: check and convert delta, its hierarchy, theta = 0. The residual at theta = 0 gives the
   // normalisation r0 and the running sum of Sigma that sets the shift of the first outer residual.
-  // Every box reduces into its own result slots, so each phase needs one synchronisation.
+  // Every box reduces into its own result slots (bad cells, sum b, sum b^2), read back once.
   std::vector<double> rh(8 * (size_t)nbox, 0.0);
-  for (int b = 0; b < nbox && e == hipSuccess; ++b) {
-    const size_t cells = (size_t)n[b] * n[b] * n[b];
-    e = launch_validate(delta[b], cells, Reduce{scratch + 64, scounter, rbuf + 8 * (size_t)b}, s);
-  }
+  for (int b = 0; b < nbox && e == hipSuccess; ++b)
+    e = launch_intake(delta[b], const_cast<double*>(hb[b].lv[0].delta), n[b], true, nullptr,
+                      Reduce{scratch + 64, scounter, rbuf + 8 * (size_t)b}, s);
   if (e == hipSuccess) e = hipMemcpyAsync(rh.data(), rbuf, rh.size() * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return hip_fail(e, "batched setup");
-  for (int b = 0; b < nbox; ++b)
-    if (rh[8 * (size_t)b] != 0.0) return fail(MR_EDOMAIN, "batched: box %d has a non-finite value or 1 + delta <= 0", b);
   for (int b = 0; b < nbox && e == hipSuccess; ++b) {
     const SizeClass& c = cls[cls_of_n[n[b]]];
     const size_t cells = (size_t)c.n * c.n * c.n;
     BBox& x = hb[b];
-    e = launch_to_split(delta[b], const_cast<double*>(x.lv[0].delta), c.n, s);
     for (int l = 1; l < c.nlev && e == hipSuccess; ++l)
       e = launch_restrict(x.lv[l - 1].delta, const_cast<double*>(x.lv[l].delta), c.ns[l - 1], s);
     if (e == hipSuccess) e = hipMemsetAsync(x.theta, 0, cells * sizeof(double), s);
     for (int l = 0; l < c.nlev && e == hipSuccess; ++l) e = hipMemsetAsync(x.lv[l].lsum, 0, 4 * sizeof(double), s);
     if (e == hipSuccess) e = hipMemsetAsync(x.counter, 0, 16 * sizeof(unsigned), s);
-    if (e == hipSuccess)
-      e = launch_residual(nullptr, x.lv[0].delta, c.n, 1.0, ShiftRef{nullptr, 0.0, 0.0}, nullptr,
-                          Reduce{scratch + 64, scounter, rbuf + 8 * (size_t)b}, s);
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(rh.data(), rbuf, rh.size() * sizeof(double), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "batched setup");
+  for (int b = 0; b < nbox; ++b)
+    if (rh[8 * (size_t)b] != 0.0) return fail(MR_EDOMAIN, "batched: box %d has a non-finite value or 1 + delta <= 0", b);
   std::vector<BStat> hs(nbox);
   std::vector<double> resinit(8 * (size_t)nbox, 0.0);
   for (int b = 0; b < nbox; ++b) {
     const double cells = (double)n[b] * n[b] * n[b];
-    const double s0 = rh[8 * (size_t)b], s1 = rh[8 * (size_t)b + 1];
+    const double s0 = rh[8 * (size_t)b + 1], s1 = rh[8 * (size_t)b + 2];
     const double var = s1 - s0 * s0 / cells;
     BStat& st = hs[b];
     st = BStat{};

@@ -95,14 +95,14 @@ struct Ctx {
   int dev_alloc(double** p, size_t count);
   Reduce reducer(int slot);
   int read_scalars(int slot, int count, double* out);
-  int write_scalar(int slot, double v);
+  int write_scalars(int slot, double v0, double v1, int count = 2);
   double* lsum(int l) { return scal + kSlotLevel + 3 * l; }
   int sweep(int l);
   int down(int l, double* norm_sums);
   int up(int l);
   int vcycle(int l);
   int finest_norm(const double* theta_split, ShiftRef sh, double* nrm, double* msig);
-  int prepare(const double* delta_natural);
+  int prepare(const double* delta_natural, double* nrm0 = nullptr, double* msig0 = nullptr);
   int solve_fp64(const double* delta, double* theta, mr_info* info, int aa_depth = 0);
   int aa_reserve(int depth);
   int aa_step(AAState& st, double* iterate, const float* correction = nullptr);

@@ -239,8 +239,13 @@ hipError_t launch_residual(const double* theta, const double* delta, int n, doub
 hipError_t launch_to_split(const double* natural, double* split, int n, hipStream_t s);
 hipError_t launch_from_split(const double* split, double* natural, int n, const double* sum, double scale,
                              hipStream_t s);
-// result[0] = number of entries with a non-finite value or 1 + value <= 0.
-hipError_t launch_validate(const double* delta, size_t cells, Reduce red, hipStream_t s);
+// natural delta -> colour-split; result[0] = number of entries with a non-finite value or 1 + value
+// <= 0 and, with norm, result[1..2] = (sum b, sum b^2) of b = -Sigma at theta = 0 (h = 1); seed (may
+// be null) receives (-sum b, 0).
+hipError_t launch_intake(const double* natural, double* split, int n, bool norm, double* seed, Reduce red,
+                         hipStream_t s);
+// dst[0] = v0, dst[1] = v1 (count of them, 1 or 2)
+hipError_t launch_set_scalars(double* dst, double v0, double v1, int count, hipStream_t s);
 // result[0] = sum of a (size cells).
 hipError_t launch_sum(const double* a, size_t cells, Reduce red, hipStream_t s);
 hipError_t launch_cast32(const double* src, float* dst, size_t cells, hipStream_t s);

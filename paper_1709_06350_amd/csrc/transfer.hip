@@ -1,14 +1,68 @@
 // Grid-transfer, residual, layout and reduction kernels of the FAS cycle (Sec. II.A.3), FP64.
 //
 // Fields are colour-split (mr_device.h) unless named "natural". Streaming kernels use a 3D grid
-// (k within a row, then j, then i) so no index division is needed; reducing kernels walk rows
-// with a capped 1D grid and the deterministic grid_sum.
+// (k within a row, then j, then i) so no index division is needed. The streaming reductions write
+// one partial per block and value and a one-block launch adds them in a fixed order: an arrival
+// counter in the kernel itself (grid_sum) costs a release, an L2 write-back, per block, which took
+// 113 us of a 4096-block residual of 128^3 cells whose data moves in about 5.
+#include <algorithm>
+
 #include "mr_device.h"
 #include "mr_kernels.h"
 
 namespace mr {
 
 constexpr int kReduceGrid = 4096;
+constexpr int kFinishThreads = 1024;
+
+// One partial per value and block (thread 0 writes).
+template <int NV>
+__device__ __forceinline__ void block_partials(double (&v)[NV], double* __restrict__ partials) {
+  __shared__ double red[16][NV];
+  block_sum<NV>(v, red, threadIdx.x, blockDim.x);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) partials[(size_t)blockIdx.x * NV + c] = v[c];
+  }
+}
+
+// result[c] = sum over blocks of partials[block][c], in a fixed order (one block). With seed set,
+// seed[0] = -result[seed_from] and seed[1] = 0: the running sums of Sigma of a level whose reduced
+// values are b = -Sigma.
+template <int NV>
+__global__ void __launch_bounds__(kFinishThreads) finish_sums_kernel(const double* __restrict__ partials, int nblocks,
+                                                                     double* __restrict__ result,
+                                                                     double* __restrict__ seed, int seed_from) {
+  __shared__ double red[16][NV];
+  double v[NV];
+#pragma unroll
+  for (int c = 0; c < NV; ++c) v[c] = 0.0;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nblocks; b += kFinishThreads) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) v[c] += partials[(size_t)b * NV + c];
+  }
+  block_sum<NV>(v, red, threadIdx.x, kFinishThreads);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) result[c] = v[c];
+    if (seed) {
+#pragma unroll
+      for (int c = 0; c < NV; ++c)
+        if (c == seed_from) seed[0] = -v[c];
+      seed[1] = 0.0;
+    }
+  }
+}
+
+template <int NV>
+static hipError_t finish_sums(int nblocks, Reduce red, double* seed, int seed_from, hipStream_t s) {
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((finish_sums_kernel<NV>), dim3(1), dim3(kFinishThreads), 0, s, (const double*)red.partials, nblocks,
+                     red.result, seed, seed_from);
+  return hipGetLastError();
+}
 
 __device__ __forceinline__ double shift_value(const ShiftRef& c) {
   return (c.c_sum ? (c.c_sum[0] + c.c_sum[1]) * c.c_scale : 0.0) + c.c_add;
@@ -42,7 +96,7 @@ __global__ void __launch_bounds__(256) tau_kernel(const double* __restrict__ th,
 
 __global__ void __launch_bounds__(256) residual_kernel(const double* __restrict__ theta,
     const double* __restrict__ delta, int n, double ih2, ShiftRef sref, double* __restrict__ r_nat,
-    Reduce red) {
+    double* __restrict__ partials) {
   const double sh = shift_value(sref);
   double a0 = 0.0, a1 = 0.0;
   const int rows = n * n;
@@ -70,7 +124,7 @@ __global__ void __launch_bounds__(256) residual_kernel(const double* __restrict_
     }
   }
   double v[2] = {a0, a1};
-  grid_sum<2>(v, red.partials, red.counter, red.result, gridDim.x, blockIdx.x);
+  block_partials<2>(v, partials);
 }
 
 // that <- tc - that on the coarse mesh (the coarse correction, formed once before prolongation).
@@ -271,22 +325,74 @@ __global__ void __launch_bounds__(1024) from_split_kernel(const double* __restri
   nat[((size_t)i * n + j) * n + k] = sp[split_idx(n, i, j, k)] - mshift;
 }
 
-__global__ void __launch_bounds__(256) validate_kernel(const double* __restrict__ delta, size_t cells, Reduce red) {
-  double bad = 0.0;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < cells; e += (size_t)gridDim.x * blockDim.x) {
-    const double v = 1.0 + delta[e];
-    if (!(v > 0.0) || !__builtin_isfinite(v)) bad += 1.0;
+// The caller's delta into the colour-split layout, with the number of cells that are not finite or
+// have 1 + delta <= 0 and (NORM) the sums of b = -Sigma(theta = 0) and b^2 of the reference norm:
+// partials[block] = (bad cells, sum b, sum b^2). One read and one write of the mesh, where the
+// check, the conversion and the norm in passes of their own took 374 + 442 + 551 us at 512^3.
+// A block takes whole strips: per = 256 / n rows (n <= 256) or 256 cells of a row, four strips in
+// flight.
+template <bool NORM>
+__global__ void __launch_bounds__(256) intake_kernel(const double* __restrict__ nat, double* __restrict__ sp, int n,
+                                                     float inv_n, double* __restrict__ partials) {
+  constexpr int U = 4;
+  const int nh = n >> 1, rows = n * n;
+  const unsigned half = (unsigned)rows * (unsigned)nh;
+  const int per = n <= 256 ? 256 / n : 1;         // rows of a strip
+  const int kp = n <= 256 ? 1 : (n + 255) >> 8;   // strips of a row
+  const int r = n <= 256 ? (int)threadIdx.x / n : 0;
+  const int k0 = n <= 256 ? (int)threadIdx.x - r * n : (int)threadIdx.x;
+  const int strips = n <= 256 ? (rows + per - 1) / per : rows * kp;
+  const Nb18 zero = {};
+  double bad = 0.0, a0 = 0.0, a1 = 0.0;
+  for (int s0 = blockIdx.x; s0 < strips; s0 += U * gridDim.x) {
+    double d[U];
+    int row[U], k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int st = s0 + u * (int)gridDim.x;
+      row[u] = n <= 256 ? st * per + r : st / kp;
+      k[u] = n <= 256 ? k0 : (st - row[u] * kp) * 256 + k0;
+      if (st >= strips || r >= per || row[u] >= rows || k[u] >= n) row[u] = -1;
+      d[u] = row[u] >= 0 ? nat[(size_t)row[u] * n + k[u]] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (row[u] < 0) continue;
+      // row < 2^20: the product is within half a unit of the exact quotient's cell
+      const int i = (int)(((float)row[u] + 0.5f) * inv_n), j = row[u] - i * n;
+      sp[((i + j + k[u]) & 1) * half + (unsigned)row[u] * (unsigned)nh + (unsigned)(k[u] >> 1)] = d[u];
+      const double v = 1.0 + d[u];
+      if (!(v > 0.0) || !__builtin_isfinite(v)) bad += 1.0;
+      if (NORM) {
+        double S;
+        const double b = -sigma_cell(zero, v, 1.0, S);
+        a0 += b;
+        a1 += b * b;
+      }
+    }
   }
-  double v[1] = {bad};
-  grid_sum<1>(v, red.partials, red.counter, red.result, gridDim.x, blockIdx.x);
+  double v[3] = {bad, a0, a1};
+  block_partials<3>(v, partials);
 }
 
-__global__ void __launch_bounds__(256) sum_kernel(const double* __restrict__ a, size_t cells, Reduce red) {
-  double s = 0.0;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < cells; e += (size_t)gridDim.x * blockDim.x)
-    s += a[e];
-  double v[1] = {s};
-  grid_sum<1>(v, red.partials, red.counter, red.result, gridDim.x, blockIdx.x);
+__global__ void __launch_bounds__(256) sum_kernel(const double* __restrict__ a, size_t cells,
+                                                  double* __restrict__ partials) {
+  constexpr int U = 4;
+  const size_t step = (size_t)gridDim.x * blockDim.x;
+  double s[U] = {};
+  size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  for (; e + (U - 1) * step < cells; e += U * step) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) s[u] += a[e + u * step];
+  }
+  for (; e < cells; e += step) s[0] += a[e];
+  double v[1] = {(s[0] + s[1]) + (s[2] + s[3])};
+  block_partials<1>(v, partials);
+}
+
+__global__ void set_scalars_kernel(double* dst, double v0, double v1, int count) {
+  if (threadIdx.x == 0) dst[0] = v0;
+  if (threadIdx.x == 1 && count > 1) dst[1] = v1;
 }
 
 // ---- launchers ----------------------------------------------------------------------------
@@ -298,6 +404,9 @@ static int lin_grid(size_t cells) {
   size_t b = (cells + 255) / 256;
   return (int)(b < 1 ? 1 : (b > (size_t)kReduceGrid ? kReduceGrid : b));
 }
+// Blocks of a streaming reduction: at least four elements (strips) a thread, at most eight resident
+// blocks on each of 256 compute units.
+static int stream_grid(size_t strips) { return (int)std::min<size_t>(2048, std::max<size_t>(1, (strips + 3) / 4)); }
 static int row_threads(int n) { return n < 64 ? 64 : (n < 256 ? n : 256); }
 
 hipError_t launch_tau(const double* th, const double* delta, const double* rd, double* f, int n,
@@ -326,8 +435,8 @@ hipError_t launch_restrict(const double* fine, double* coarse, int n, hipStream_
 hipError_t launch_residual(const double* theta, const double* delta, int n, double h, ShiftRef shift,
                            double* r_natural, Reduce red, hipStream_t s) {
   hipLaunchKernelGGL(residual_kernel, dim3(rows_grid(n)), dim3(row_threads(n)), 0, s, theta, delta, n,
-                     1.0 / (h * h), shift, r_natural, red);
-  return hipGetLastError();
+                     1.0 / (h * h), shift, r_natural, red.partials);
+  return finish_sums<2>(rows_grid(n), red, nullptr, 0, s);
 }
 
 hipError_t launch_to_split(const double* natural, double* split, int n, hipStream_t s) {
@@ -341,13 +450,25 @@ hipError_t launch_from_split(const double* split, double* natural, int n, const 
   return hipGetLastError();
 }
 
-hipError_t launch_validate(const double* delta, size_t cells, Reduce red, hipStream_t s) {
-  hipLaunchKernelGGL(validate_kernel, dim3(lin_grid(cells)), dim3(256), 0, s, delta, cells, red);
-  return hipGetLastError();
+hipError_t launch_intake(const double* natural, double* split, int n, bool norm, double* seed, Reduce red,
+                         hipStream_t s) {
+  const size_t strips = n <= 256 ? ((size_t)n * n + 256 / n - 1) / (256 / n) : (size_t)n * n * ((n + 255) / 256);
+  const int nb = stream_grid(strips);
+  if (norm)
+    hipLaunchKernelGGL((intake_kernel<true>), dim3(nb), dim3(256), 0, s, natural, split, n, 1.0f / (float)n, red.partials);
+  else
+    hipLaunchKernelGGL((intake_kernel<false>), dim3(nb), dim3(256), 0, s, natural, split, n, 1.0f / (float)n, red.partials);
+  return finish_sums<3>(nb, red, seed, 1, s);
 }
 
 hipError_t launch_sum(const double* a, size_t cells, Reduce red, hipStream_t s) {
-  hipLaunchKernelGGL(sum_kernel, dim3(lin_grid(cells)), dim3(256), 0, s, a, cells, red);
+  const int nb = stream_grid((cells + 255) / 256);
+  hipLaunchKernelGGL(sum_kernel, dim3(nb), dim3(256), 0, s, a, cells, red.partials);
+  return finish_sums<1>(nb, red, nullptr, 0, s);
+}
+
+hipError_t launch_set_scalars(double* dst, double v0, double v1, int count, hipStream_t s) {
+  hipLaunchKernelGGL(set_scalars_kernel, dim3(1), dim3(64), 0, s, dst, v0, v1, count);
   return hipGetLastError();
 }
 

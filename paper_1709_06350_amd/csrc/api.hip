@@ -130,9 +130,11 @@ int Ctx::dev_alloc(double** p, size_t count) {
 
 Reduce Ctx::reducer(int slot) { return Reduce{partials, counter, scal + slot}; }
 
-int Ctx::read_scalars(int slot, int count, double* out) {
-  if (count > kHostSlots - 16) return fail(MR_EINVAL, "read_scalars: too many values");
-  hipError_t e = hipMemcpyAsync(host, scal + slot, count * sizeof(double), hipMemcpyDeviceToHost, stream);
+int Ctx::read_scalars(int slot, int count, double* out) { return read_device(scal + slot, count, out); }
+
+int Ctx::read_device(const double* from, int count, double* out) {
+  if (count > kHostSlots) return fail(MR_EINVAL, "read back: too many values");
+  hipError_t e = hipMemcpyAsync(host, from, count * sizeof(double), hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return hip_fail(e, "read back");
   for (int i = 0; i < count; ++i) out[i] = host[i];
@@ -295,6 +297,110 @@ int Ctx::sweep(int l) {
   return MR_OK;
 }
 
+// The block form of the cycle: down launch, up launch and tail workgroup. part holds, in slots of
+// kBlkMaxBlocks: sums of the down launch, defect, defect^2 (these two and C contiguous), up launch.
+static double* part_c(const Level& L) { return L.part; }
+static double* part_d(const Level& L) { return L.part + kBlkMaxBlocks; }
+static double* part_u(const Level& L) { return L.part + 3 * kBlkMaxBlocks + 8; }
+
+// First level of the block form (nlev: none): the levels from it to the coarsest are all small
+// enough, run their default schedules and the default cycle of two sweeps before and after. The
+// finest level keeps its timed sweeps while the caller times them.
+int Ctx::blk_first() const {
+  if ((opts.flags & (MR_FLAG_ORDER4 | MR_FLAG_TWO_PASS)) || opts.npre != 2 || opts.npost != 2) return nlev;
+  int t = 0;
+  while (t < nlev && lv[t].n > 12) ++t;
+  if (t == 0 || t >= nlev || !lv[t].rd || lv[t].pinned) return nlev;
+  // tail forms: 8^3 over 4^3, 12^3 over 6^3, 10^3 alone
+  if (lv[t].n == 10 ? t != nlev - 1 : (lv[t].n != 8 && lv[t].n != 12) || t != nlev - 2) return nlev;
+  const int lowest = timer.on ? 1 : 0;
+  while (t > lowest && lv[t - 1].part && !lv[t - 1].pinned) --t;
+  return t;
+}
+
+int Ctx::blk_down(int l, const double* c_part, int c_count, double c_scale) {
+  Level& L = lv[l];
+  Level& Lc = lv[l + 1];
+  const int nb = blk_blocks(L.n);
+  BlkDownArgs a{};
+  a.theta = l == 0 ? L.th[L.cur] : L.that;
+  a.delta = L.delta;
+  a.rd = l == 0 ? nullptr : L.rd;
+  a.n = L.n;
+  a.h2 = L.h * L.h;
+  a.ih2 = 1.0 / a.h2;
+  a.c_part = c_part;
+  a.c_count = c_count;
+  a.c_scale = c_scale;
+  L.cur = l == 0 ? L.cur ^ 1 : 0;
+  a.theta_out = L.th[L.cur];
+  a.f_out = l == 0 ? nullptr : L.f;
+  a.theta_c = Lc.that;
+  a.rd_c = Lc.rd;
+  a.part_c = part_c(L);
+  a.part_d = part_d(L);
+  a.part_d2 = part_d(L) + nb;
+  a.c_out = part_d(L) + 2 * nb;
+  hipError_t e = launch_blk_down(a, stream);
+  return e == hipSuccess ? MR_OK : hip_fail(e, "block down");
+}
+
+int Ctx::blk_up(int l) {
+  Level& L = lv[l];
+  Level& Lc = lv[l + 1];
+  const int nb = blk_blocks(L.n);
+  BlkUpArgs a{};
+  a.theta = L.th[L.cur];
+  a.delta = L.delta;
+  a.f = l == 0 ? nullptr : L.f;
+  a.theta_c = Lc.th[Lc.cur];
+  a.that_c = Lc.that;
+  a.n = L.n;
+  a.h2 = L.h * L.h;
+  a.ih2 = 1.0 / a.h2;
+  a.c_part = part_c(L);
+  a.c_count = nb;
+  a.c_scale = 1.0 / (double)L.cells;
+  L.cur ^= 1;
+  a.theta_out = L.th[L.cur];
+  a.part_c = part_u(L);
+  L.cp = part_u(L);
+  L.cp_count = nb;
+  hipError_t e = launch_blk_up(a, stream);
+  return e == hipSuccess ? MR_OK : hip_fail(e, "block up");
+}
+
+// The cycle of level l >= 1 and below from that, rd: the result is th[cur]. C of the level is the
+// mean of Sigma + f, which at the restricted iterate is minus the mean of the restricted defect.
+int Ctx::blk_cycle(int l, const double* c_part, int c_count, double c_scale) {
+  Level& L = lv[l];
+  if (L.n <= 12) {
+    BlkTailArgs a{};
+    a.that = L.that;
+    a.delta = L.delta;
+    a.rd = L.rd;
+    a.coarsest = l == nlev - 1;
+    a.delta_c = a.coarsest ? nullptr : lv[l + 1].delta;
+    a.n = L.n;
+    a.npre = opts.npre;
+    a.npost = opts.npost;
+    a.ncoarse = opts.ncoarse;
+    a.h2 = L.h * L.h;
+    a.ih2 = 1.0 / a.h2;
+    a.c_part = c_part;
+    a.c_count = c_count;
+    a.c_scale = c_scale;
+    L.cur = 0;
+    a.theta_out = L.th[0];
+    hipError_t e = launch_blk_tail(a, stream);
+    return e == hipSuccess ? MR_OK : hip_fail(e, "block tail");
+  }
+  int rc;
+  if ((rc = blk_down(l, c_part, c_count, c_scale)) != MR_OK) return rc;
+  if ((rc = blk_cycle(l + 1, part_d(L), blk_blocks(L.n), -1.0 / (double)L.cells)) != MR_OK) return rc;
+  return blk_up(l);
+}
+
 // Pre-relaxation on level l, then the fused defect + restriction onto level l+1 (theta_c into
 // the coarse iterate and the saved copy, R d into the coarse f). norm_sums (device, 2 values)
 // receives sum d and sum d^2 of level l when given.
@@ -304,6 +410,7 @@ int Ctx::down(int l, double* norm_sums) {
     if ((rc = sweep(l)) != MR_OK) return rc;
   Level& L = lv[l];
   Level& Lc = lv[l + 1];
+  const bool to_blk = l + 1 >= blk_first();
   DefectArgs a{};
   a.theta = L.th[L.cur];
   a.delta = L.delta;
@@ -313,9 +420,9 @@ int Ctx::down(int l, double* norm_sums) {
   a.c_sum = lsum(l);
   a.c_scale = 1.0 / (double)L.cells;
   a.c_add = 0.0;
-  a.theta_c = Lc.th[Lc.cur];
-  a.theta_c2 = Lc.that;
-  a.dr = Lc.f;
+  a.theta_c = to_blk ? Lc.that : Lc.th[Lc.cur];
+  a.theta_c2 = to_blk ? nullptr : Lc.that;
+  a.dr = to_blk ? Lc.rd : Lc.f;
   a.sums_out = norm_sums ? norm_sums : scal + kSlotAux + 14;
   a.partials = partials;
   a.counter = counter;
@@ -324,13 +431,19 @@ int Ctx::down(int l, double* norm_sums) {
 }
 
 // Coarse-grid correction of level l from level l+1 and post-relaxation on level l.
-int Ctx::up(int l) {
+int Ctx::up(int l, const double* norm_sums) {
   Level& L = lv[l];
   Level& Lc = lv[l + 1];
-  hipError_t e = launch_tau(Lc.that, Lc.delta, Lc.f, Lc.f, Lc.n, Lc.h, reducer(kSlotLevel + 3 * (l + 1)), stream);
-  if (e != hipSuccess) return hip_fail(e, "tau");
+  hipError_t e = hipSuccess;
   int rc;
-  if ((rc = vcycle(l + 1)) != MR_OK) return rc;
+  if (l + 1 >= blk_first()) {
+    const double* sums = norm_sums ? norm_sums : scal + kSlotAux + 14;
+    if ((rc = blk_cycle(l + 1, sums, 1, -1.0 / (double)L.cells)) != MR_OK) return rc;
+  } else {
+    e = launch_tau(Lc.that, Lc.delta, Lc.f, Lc.f, Lc.n, Lc.h, reducer(kSlotLevel + 3 * (l + 1)), stream);
+    if (e != hipSuccess) return hip_fail(e, "tau");
+    if ((rc = vcycle(l + 1)) != MR_OK) return rc;
+  }
   e = launch_prolong_correct(Lc.th[Lc.cur], Lc.that, L.th[L.cur], L.n, stream);
   if (e != hipSuccess) return hip_fail(e, "prolong_correct");
   for (int s = 0; s < opts.npost; ++s)
@@ -357,7 +470,7 @@ int Ctx::vcycle(int l) {
   }
   int rc;
   if ((rc = down(l, nullptr)) != MR_OK) return rc;
-  return up(l);
+  return up(l, nullptr);
 }
 
 // Residual of the finest level with a given shift: b = nabla^2 theta - Sigma + shift;
@@ -431,6 +544,9 @@ int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_de
   int cyc = 0;
   int status = MR_OK;
   double best = rel;
+  const bool blk0 = blk_first() == 0;
+  L0.cp = lsum(0);
+  L0.cp_count = 2;
   // Each cycle: pre-relaxation, then the defect pass, whose sums give the residual norm of the
   // current iterate (convergence test); if not converged, coarse correction and post-relaxation.
   while (rel > opts.tol && cyc < opts.max_cycles) {
@@ -438,12 +554,28 @@ int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_de
       e = aa_save(*this, L0.th[L0.cur]);
       if (e != hipSuccess) return hip_fail(e, "Anderson save");
     }
-    if ((rc = down(0, scal + kSlotRes)) != MR_OK) return rc;
-    double r[kSlotRes + 2];
-    if ((rc = read_scalars(0, kSlotRes + 2, r)) != MR_OK) return rc;
-    const double var = r[kSlotRes + 1] - r[kSlotRes] * r[kSlotRes] / N3;
+    double shift, sd = 0.0, sd2 = 0.0;   // C, sum d and sum d^2 of the defect pass
+    if (blk0) {
+      const int nb = blk_blocks(L0.n);
+      if ((rc = blk_down(0, L0.cp, L0.cp_count, 1.0 / N3)) != MR_OK) return rc;
+      std::vector<double> r(2 * nb + 1);
+      if ((rc = read_device(part_d(L0), 2 * nb + 1, r.data())) != MR_OK) return rc;
+      for (int b = 0; b < nb; ++b) {
+        sd += r[b];
+        sd2 += r[nb + b];
+      }
+      shift = r[2 * nb];
+    } else {
+      if ((rc = down(0, scal + kSlotRes)) != MR_OK) return rc;
+      double r[kSlotRes + 2];
+      if ((rc = read_scalars(0, kSlotRes + 2, r)) != MR_OK) return rc;
+      sd = r[kSlotRes];
+      sd2 = r[kSlotRes + 1];
+      shift = (r[0] + r[1]) / N3;
+    }
+    const double var = sd2 - sd * sd / N3;
     nrm = std::sqrt(var > 0.0 ? var : 0.0);
-    msig = (r[0] + r[1]) / N3 - r[kSlotRes] / N3;
+    msig = shift - sd / N3;
     rel = nrm / r0;
     ++cyc;
     if (cyc < 128) loc.history[cyc] = rel;
@@ -453,7 +585,13 @@ int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_de
     }
     if (rel < best) best = rel;
     if (rel <= opts.tol || cyc >= opts.max_cycles) break;
-    if ((rc = up(0)) != MR_OK) return rc;
+    if (blk0) {
+      rc = blk_cycle(1, part_d(L0), blk_blocks(L0.n), -1.0 / N3);
+      if (rc == MR_OK) rc = blk_up(0);
+    } else {
+      rc = up(0, scal + kSlotRes);
+    }
+    if (rc != MR_OK) return rc;
     if (aa_depth > 0 && (rc = aa_step(aa, L0.th[L0.cur])) != MR_OK) return rc;
   }
   if (status == MR_OK && rel > opts.tol) {
@@ -548,8 +686,14 @@ int mr_create(mr_ctx** out, int n, const mr_opts* opts, void* hip_stream) {
       mr_destroy(reinterpret_cast<mr_ctx*>(c));
       return rc;
     }
+    if (blk_level_supported(L.n) && (rc = c->dev_alloc(&L.part, 4 * kBlkMaxBlocks + 8)) != MR_OK) {
+      mr_destroy(reinterpret_cast<mr_ctx*>(c));
+      return rc;
+    }
     if (l == 0) continue;
-    if ((rc = c->dev_alloc(&L.that, L.cells)) != MR_OK || (rc = c->dev_alloc(&L.f, L.cells)) != MR_OK) {
+    const bool blk = L.n <= 12 || blk_level_supported(L.n);
+    if ((rc = c->dev_alloc(&L.that, L.cells)) != MR_OK || (rc = c->dev_alloc(&L.f, L.cells)) != MR_OK ||
+        (blk && (rc = c->dev_alloc(&L.rd, L.cells)) != MR_OK)) {
       mr_destroy(reinterpret_cast<mr_ctx*>(c));
       return rc;
     }
@@ -681,6 +825,7 @@ int mr_set_schedule(mr_ctx* h, int level, const int sched[4]) {
     L.fz.tiles_m = nh / tm;
     L.fz.nchunks = nch;
     L.has_fz = true;
+    L.pinned = true;
     return MR_OK;
   }
   TileCfg t;
@@ -705,6 +850,7 @@ int mr_set_schedule(mr_ctx* h, int level, const int sched[4]) {
   }
   L.sw = t;
   L.has_fz = false;
+  L.pinned = true;
   return MR_OK;
 }
 

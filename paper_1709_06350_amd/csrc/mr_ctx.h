@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "block_cycle.h"
 #include "mr.h"
 #include "mr_kernels.h"
 
@@ -25,7 +26,7 @@ constexpr int kSlotLin = 64;     // 3 per level: running sums of the linear (FP3
 constexpr int kSlotBase = 112;   // 2 values: 2^-s, 2^s of the fixed-point base of the mixed form
 constexpr int kSlotTmax = 114;   // max |theta| (as the bits of a non-negative double; zero between uses)
 constexpr int kSlotCount = 128;
-constexpr int kHostSlots = 80;
+constexpr int kHostSlots = 1040;   // host copies of scalars, or of the block sums of a finest mesh in the block form
 
 // One mesh of the hierarchy. All fields colour-split; th[0], th[1] are the ping-pong buffers
 // (both colours each), th[cur] the current iterate.
@@ -41,6 +42,14 @@ struct Level {
   TileCfg sw, df;           // tiles of the half-sweep and of the defect + restriction
   FusedCfg fz;              // tile of the fused red-black sweep (has_fz: one fits)
   bool has_fz = false;
+  bool pinned = false;      // schedule set by the caller: the level runs its own sweeps
+  // Block form of the cycle (block_cycle.hip) on small levels: restricted defect, block sums
+  // (Sigma + f of the down launch; defect, defect^2, shift; Sigma + f of the up launch), and where
+  // the next down launch of a finest level finds the sums of its shift.
+  double* rd = nullptr;
+  double* part = nullptr;
+  const double* cp = nullptr;
+  int cp_count = 0;
 };
 
 struct EventTimer {
@@ -95,12 +104,17 @@ struct Ctx {
   int dev_alloc(double** p, size_t count);
   Reduce reducer(int slot);
   int read_scalars(int slot, int count, double* out);
+  int read_device(const double* from, int count, double* out);
   int write_scalars(int slot, double v0, double v1, int count = 2);
   double* lsum(int l) { return scal + kSlotLevel + 3 * l; }
   int sweep(int l);
   int down(int l, double* norm_sums);
-  int up(int l);
+  int up(int l, const double* norm_sums);
   int vcycle(int l);
+  int blk_first() const;
+  int blk_down(int l, const double* c_part, int c_count, double c_scale);
+  int blk_up(int l);
+  int blk_cycle(int l, const double* c_part, int c_count, double c_scale);
   int finest_norm(const double* theta_split, ShiftRef sh, double* nrm, double* msig);
   int prepare(const double* delta_natural, double* nrm0 = nullptr, double* msig0 = nullptr);
   int solve_fp64(const double* delta, double* theta, mr_info* info, int aa_depth = 0);

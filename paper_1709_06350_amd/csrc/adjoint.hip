@@ -22,6 +22,7 @@
 #include <utility>
 #include <vector>
 
+#include "adj_block.h"
 #include "mr.h"
 #include "mr_ctx.h"
 #include "mr_device.h"
@@ -37,6 +38,8 @@ struct AdjLevel {
   double* coef = nullptr;   // 6 fields: A_x, A_y, A_z, W_xy, W_xz, W_yz (each colour-split n^3)
   int tm = 0, tj = 0, ci = 0;   // half-sweep tile and chunk; tm == 0: the row kernel
   bool pfc = false;             // coefficient prefetch of the tiled half-sweep
+  double* part = nullptr;       // block form: sums of the down launch, squared residuals, sums of the up launch
+  AdjMu mu{nullptr, 0, 0.0};    // ... and where the offset of lam[cur] is found
 };
 
 struct AdjointState {
@@ -470,20 +473,10 @@ __global__ void __launch_bounds__(1024) adj_grad_kernel(const double* __restrict
   grad[((size_t)i * n + j) * n + k] = D[g] * (lam[g] - mu);
 }
 
-__global__ void __launch_bounds__(256) center_kernel(double* __restrict__ a, size_t cells, const double* sum, double scale) {
-  const double m = (*sum) * scale;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < cells; e += (size_t)gridDim.x * blockDim.x)
-    a[e] -= m;
-}
-
 // ---- driver -------------------------------------------------------------------------------
 
 static int rows_blocks_a(int n) { return n * n < 4096 ? n * n : 4096; }
 static int row_threads_a(int n) { return n < 64 ? 64 : (n < 256 ? n : 256); }
-static int lin_blocks_a(size_t cells) {
-  size_t b = (cells + 255) / 256;
-  return (int)(b < 1 ? 1 : (b > 4096 ? 4096 : b));
-}
 
 // ---- half-sweep launch and tile choice ----------------------------------------------------
 
@@ -649,6 +642,7 @@ static int adjoint_alloc(Ctx* c) {
     if ((rc = get(&L.lam[0], cells)) != MR_OK || (rc = get(&L.lam[1], cells)) != MR_OK ||
         (rc = get(&L.rhs, cells)) != MR_OK || (rc = get(&L.coef, 6 * cells)) != MR_OK)
       return rc;
+    if (blk_level_supported(c->lv[l].n) && (rc = get(&L.part, 3 * kBlkMaxBlocks)) != MR_OK) return rc;
   }
   if ((rc = get(&a->D, c->lv[0].cells)) != MR_OK) return rc;
   // half-sweep schedule per level, timed on the level's zeroed buffers
@@ -729,9 +723,93 @@ int Ctx::adj_sweep(int l) {
   return MR_OK;
 }
 
+// First level of the block form (adj_block.hip; nlev: none): the default cycle of two sweeps before and
+// after, no forced kernel, and only small levels from there to the coarsest.
+int Ctx::adj_blk_first() const {
+  if ((opts.flags & (MR_FLAG_ADJ_ROWS | MR_FLAG_ADJ_TILED)) || opts.npre != 2 || opts.npost != 2) return nlev;
+  int t = 0;
+  while (t < nlev && lv[t].n > 12) ++t;
+  if (t == 0 || t >= nlev || !tail_form(t)) return nlev;
+  while (t > 0 && adj->lv[t - 1].part) --t;
+  return t;
+}
+
+// The cycle of a level in the block form: from lambda = 0 below the finest level. A.mu holds the
+// offset of lam[cur] afterwards. r2 (host, finest level): receives the squared residual norm after
+// the pre-smoothing, and the cycle stops there once its root is at or below adj_stop.
+int Ctx::adj_blk_cycle(int l, double* r2) {
+  AdjLevel& A = adj->lv[l];
+  Level& F = lv[l];
+  hipError_t e;
+  if (F.n <= 12) {
+    AdjTailArgs a{};
+    a.rhs = A.rhs;
+    a.coef = A.coef;
+    a.coef_c = l == nlev - 1 ? nullptr : adj->lv[l + 1].coef;
+    a.n = F.n;
+    a.npre = opts.npre;
+    a.npost = opts.npost;
+    a.ncoarse = opts.ncoarse;
+    a.h2 = F.h * F.h;
+    A.cur = 0;
+    a.lam_out = A.lam[0];
+    A.mu = AdjMu{nullptr, 0, 0.0};
+    e = launch_adj_tail(a, stream);
+    return e == hipSuccess ? MR_OK : hip_fail(e, "adjoint tail");
+  }
+  const int nb = blk_blocks(F.n);
+  const double scale = 1.0 / (double)F.cells;
+  AdjLevel& Ac = adj->lv[l + 1];
+  AdjDownArgs d{};
+  d.lam = l == 0 ? A.lam[A.cur] : nullptr;
+  d.rhs = A.rhs;
+  d.coef = A.coef;
+  d.n = F.n;
+  d.h2 = F.h * F.h;
+  d.mu = A.mu;
+  A.cur = l == 0 ? A.cur ^ 1 : 0;
+  d.lam_out = A.lam[A.cur];
+  d.rhs_c = Ac.rhs;
+  d.part_s = A.part;
+  d.part_r2 = A.part + kBlkMaxBlocks;
+  if ((e = launch_adj_down(d, stream)) != hipSuccess) return hip_fail(e, "adjoint down");
+  A.mu = AdjMu{A.part, nb, scale};
+  int rc;
+  if (r2) {
+    double p[kBlkMaxBlocks];
+    if ((rc = read_device(d.part_r2, nb, p)) != MR_OK) return rc;
+    *r2 = 0.0;
+    for (int b = 0; b < nb; ++b) *r2 += p[b];
+    if (std::sqrt(*r2) <= adj_stop) return MR_OK;
+  }
+  if ((rc = adj_blk_cycle(l + 1, nullptr)) != MR_OK) return rc;
+  AdjUpArgs u{};
+  u.lam = A.lam[A.cur];
+  u.rhs = A.rhs;
+  u.coef = A.coef;
+  u.lam_c = Ac.lam[Ac.cur];
+  u.n = F.n;
+  u.h2 = d.h2;
+  u.mu = A.mu;
+  u.mu_c = Ac.mu;
+  A.cur ^= 1;
+  u.lam_out = A.lam[A.cur];
+  u.part_s = A.part + 2 * kBlkMaxBlocks;
+  if ((e = launch_adj_up(u, stream)) != hipSuccess) return hip_fail(e, "adjoint up");
+  A.mu = AdjMu{u.part_s, nb, scale};
+  return MR_OK;
+}
+
 int Ctx::adj_vcycle(int l, double* norm2) {
   AdjLevel& A = adj->lv[l];
   Level& F = lv[l];
+  const int first = adj_blk_first();
+  if (l >= first) {
+    double r2 = 0.0;
+    const int brc = adj_blk_cycle(l, norm2 ? &r2 : nullptr);
+    if (norm2) adj_last_norm = std::sqrt(r2);
+    return brc;
+  }
   const double scale = 1.0 / (double)F.cells;
   hipError_t e;
   if (l == nlev - 1) {
@@ -773,9 +851,11 @@ int Ctx::adj_vcycle(int l, double* norm2) {
                        A.lam[A.cur], A.rhs, A.coef, F.n, 1.0 / (F.h * F.h), linsum(l), scale, Ac.rhs,
                        Reduce{partials, counter, nrm});
   }
-  Ac.cur = 0;
-  if ((e = hipMemsetAsync(Ac.lam[0], 0, Fc.cells * sizeof(double), stream)) != hipSuccess) return hip_fail(e, "zero");
-  if ((e = hipMemsetAsync(linsum(l + 1), 0, 2 * sizeof(double), stream)) != hipSuccess) return hip_fail(e, "zero");
+  if (l + 1 < first) {
+    Ac.cur = 0;
+    if ((e = hipMemsetAsync(Ac.lam[0], 0, Fc.cells * sizeof(double), stream)) != hipSuccess) return hip_fail(e, "zero");
+    if ((e = hipMemsetAsync(linsum(l + 1), 0, 2 * sizeof(double), stream)) != hipSuccess) return hip_fail(e, "zero");
+  }
   if (norm2) {
     // convergence test of the finest level before the coarse correction
     double r[2];
@@ -784,6 +864,9 @@ int Ctx::adj_vcycle(int l, double* norm2) {
     if (adj_last_norm <= adj_stop) return MR_OK;
   }
   if ((rc = adj_vcycle(l + 1, nullptr)) != MR_OK) return rc;
+  if (l + 1 >= first && Ac.mu.count > 0 &&
+      (e = launch_finish(Ac.mu.part, Ac.mu.count, linsum(l + 1), stream)) != hipSuccess)
+    return hip_fail(e, "adjoint offset");
   // l += P(lc - mu_c)
   if ((e = launch_prolong_add(Ac.lam[Ac.cur], linsum(l + 1), 1.0 / (double)Fc.cells, A.lam[A.cur], F.n, stream)) !=
       hipSuccess)
@@ -817,19 +900,14 @@ int Ctx::adjoint_solve(const double* delta, const double* theta_star, const doub
   // rhs = g - <g>, lambda = 0
   if (e == hipSuccess) e = launch_to_split(g, A0.rhs, L0.n, stream);
   if (e == hipSuccess) e = launch_sum(A0.rhs, L0.cells, reducer(kSlotGauge), stream);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(center_kernel, dim3(lin_blocks_a(L0.cells)), dim3(256), 0, stream, A0.rhs, L0.cells,
-                       (const double*)(scal + kSlotGauge), 1.0 / N3);
-    e = hipGetLastError();
-  }
+  if (e == hipSuccess)   // and ||rhs||, the residual at lambda = 0
+    e = launch_center(A0.rhs, L0.cells, scal + kSlotGauge, 1.0 / N3, reducer(kSlotAux + 7), stream);
   A0.cur = 0;
+  A0.mu = AdjMu{linsum(0), 2, 1.0 / N3};
   if (e == hipSuccess) e = hipMemsetAsync(A0.lam[0], 0, L0.cells * sizeof(double), stream);
-  if (e == hipSuccess) e = hipMemsetAsync(linsum(0), 0, 3 * sizeof(double), stream);
+  if (e == hipSuccess) e = hipMemsetAsync(linsum(0), 0, 3 * (size_t)nlev * sizeof(double), stream);
   if (e != hipSuccess) return hip_fail(e, "adjoint setup");
-  // ||rhs||: the residual pass at lambda = 0
-  hipLaunchKernelGGL(adj_resid_restrict_kernel, dim3(rows_blocks_a(L0.n / 2)), dim3(row_threads_a(L0.n / 2)), 0, stream,
-                     A0.lam[0], A0.rhs, A0.coef, L0.n, 1.0, linsum(0), 1.0 / N3, adj->lv[1].rhs,
-                     Reduce{partials, counter, scal + kSlotAux + 6});
+  const bool blk0 = adj_blk_first() == 0;
   double r[2];
   if ((rc = read_scalars(kSlotAux + 6, 2, r)) != MR_OK) return rc;
   double r0 = std::sqrt(r[1] > 0.0 ? r[1] : 0.0);
@@ -860,6 +938,8 @@ int Ctx::adjoint_solve(const double* delta, const double* theta_star, const doub
     status = MR_NOT_CONVERGED;
     fail(MR_NOT_CONVERGED, "adjoint not converged after %d cycles (rel residual %g)", cyc, rel);
   }
+  if (blk0 && (e = launch_finish(A0.mu.part, A0.mu.count, linsum(0), stream)) != hipSuccess)
+    return hip_fail(e, "adjoint offset");
   hipLaunchKernelGGL(adj_grad_kernel, dim3((unsigned)L0.n * L0.n), dim3(L0.n), 0, stream, A0.lam[A0.cur],
                      (const double*)linsum(0), 1.0 / N3, adj->D, grad, L0.n);
   e = hipGetLastError();

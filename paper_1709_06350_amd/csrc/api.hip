@@ -303,6 +303,11 @@ static double* part_c(const Level& L) { return L.part; }
 static double* part_d(const Level& L) { return L.part + kBlkMaxBlocks; }
 static double* part_u(const Level& L) { return L.part + 3 * kBlkMaxBlocks + 8; }
 
+// The levels from t down are one of the compiled tails: 8^3 over 4^3, 12^3 over 6^3, 10^3 alone.
+bool Ctx::tail_form(int t) const {
+  return lv[t].n == 10 ? t == nlev - 1 : (lv[t].n == 8 || lv[t].n == 12) && t == nlev - 2;
+}
+
 // First level of the block form (nlev: none): the levels from it to the coarsest are all small
 // enough, run their default schedules and the default cycle of two sweeps before and after. The
 // finest level keeps its timed sweeps while the caller times them.
@@ -310,9 +315,7 @@ int Ctx::blk_first() const {
   if ((opts.flags & (MR_FLAG_ORDER4 | MR_FLAG_TWO_PASS)) || opts.npre != 2 || opts.npost != 2) return nlev;
   int t = 0;
   while (t < nlev && lv[t].n > 12) ++t;
-  if (t == 0 || t >= nlev || !lv[t].rd || lv[t].pinned) return nlev;
-  // tail forms: 8^3 over 4^3, 12^3 over 6^3, 10^3 alone
-  if (lv[t].n == 10 ? t != nlev - 1 : (lv[t].n != 8 && lv[t].n != 12) || t != nlev - 2) return nlev;
+  if (t == 0 || t >= nlev || !tail_form(t) || lv[t].pinned) return nlev;
   const int lowest = timer.on ? 1 : 0;
   while (t > lowest && lv[t - 1].part && !lv[t - 1].pinned) --t;
   return t;

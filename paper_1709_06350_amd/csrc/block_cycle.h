@@ -56,6 +56,10 @@ struct BlkTailArgs {
   double* theta_out;
 };
 
+struct BlkTile {
+  int ti, tj, tk;
+};
+BlkTile blk_tile(int n);   // tile of a level of n^3 cells (ti == 0: none)
 bool blk_level_supported(int n);
 int blk_blocks(int n);
 hipError_t launch_blk_down(const BlkDownArgs& a, hipStream_t s);

@@ -16,104 +16,13 @@
 // refresh it every sweep); it moves the iterates by a constant and, through its lag, by a multiple
 // of the change of <Sigma> between two cycles, and has the same fixed point. Block sums go to plain
 // partial arrays that the next launch adds in a fixed order: no arrival counters.
+#include "block_box.h"
 #include "block_cycle.h"
 #include "mr_ctx.h"
 #include "mr_device.h"
 #include "mr_kernels.h"
 
 namespace mr {
-
-// Box of T + 2 OFF cells per axis around a TI x TJ x TK tile, colour-split in LDS: [c][i][j][m] with
-// local colour c = (i + j + k) & 1 of the local coordinates and m = k >> 1. Tile origins are even, so
-// the mesh's red cells have the local colour OFF & 1.
-template <int TI, int TJ, int TK, int OFF>
-struct Box {
-  static constexpr int RI = TI + 2 * OFF, RJ = TJ + 2 * OFF, RKH = (TK + 2 * OFF) / 2;
-  static constexpr int HALF = RI * RJ * RKH;
-  static constexpr int RED = OFF & 1;
-  int i0, j0, k0, n, nh;   // mesh coordinates of local (0, 0, 0), mesh size
-
-  __device__ __forceinline__ void init(int logical, int n_) {
-    n = n_;
-    nh = n >> 1;
-    const int tk = n / TK, tj = n / TJ;
-    const int a = logical % tk, r = logical / tk;
-    k0 = a * TK - OFF;
-    j0 = (r % tj) * TJ - OFF;
-    i0 = (r / tj) * TI - OFF;
-  }
-  // colour-split index in the mesh of local cell (i, j, k) of local colour c
-  __device__ __forceinline__ unsigned mesh(int c, int i, int j, int k) const {
-    const int gi = wrapi(i0 + i, n), gj = wrapi(j0 + j, n), gk = wrapi(k0 + k, n);
-    return (unsigned)(c ^ RED) * ((unsigned)n * n * nh) + ((unsigned)gi * n + gj) * (unsigned)nh + (unsigned)(gk >> 1);
-  }
-  // 18 neighbours of the cell at position e of its colour's half (at[own colour], at[other colour]),
-  // q its parity in z
-  static __device__ __forceinline__ void gather(const double* __restrict__ own, const double* __restrict__ other, int e,
-                                                int q, Nb18& t) {
-    constexpr int DI = RJ * RKH, DJ = RKH;
-    const double* __restrict__ o = other + e;
-    const double* __restrict__ s = own + e;
-    const double* __restrict__ oq = o + q;   // column of k + 1; the one before it is that of k - 1
-    const double* __restrict__ sq = s + q;
-    t.xm = o[-DI]; t.xp = o[DI];
-    t.ym = o[-DJ]; t.yp = o[DJ];
-    t.zm = oq[-1]; t.zp = oq[0];
-    t.xpyp = s[DI + DJ]; t.xmym = s[-DI - DJ];
-    t.xpym = s[DI - DJ]; t.xmyp = s[-DI + DJ];
-    t.xpzp = sq[DI];     t.xmzm = sq[-DI - 1];
-    t.xpzm = sq[DI - 1]; t.xmzp = sq[-DI];
-    t.ypzp = sq[DJ];     t.ymzm = sq[-DJ - 1];
-    t.ypzm = sq[DJ - 1]; t.ymzp = sq[-DJ];
-  }
-};
-
-// u / D for 0 <= u < 2^13, 2 <= D < 32 (24-bit multiply; exact while u * D < 2^20).
-template <int D>
-__device__ __forceinline__ int div_small(int u) {
-  if ((D & (D - 1)) == 0) return u / D;
-  constexpr unsigned M = (1u << 20) / D + 1;
-  return (int)(__umul24((unsigned)u, M) >> 20);
-}
-
-// The cells of one local colour in the tile grown by S cells on every side, dealt to NT threads.
-// loc[t] of a thread's cell: position in its colour's half of the box, bit 16 its parity in z, bit 17
-// set inside the tile; -1 past the end. Worked out once per launch: formed again at every use the
-// divisions were a third of the half-sweeps' instructions.
-constexpr int kLocQ = 1 << 16, kLocOwn = 1 << 17, kLocPos = kLocQ - 1;
-template <class B, int TI, int TJ, int TK, int OFF, int S, int NT>
-struct Stage {
-  static constexpr int EI = TI + 2 * S, EJ = TJ + 2 * S, EKH = (TK + 2 * S) / 2;
-  static constexpr int CELLS = EI * EJ * EKH;
-  static constexpr int N = (CELLS + NT - 1) / NT;   // cells per thread
-  static constexpr int LO = OFF - S;
-  static_assert(N * NT < 8192 && B::HALF < kLocQ, "packed positions");
-  int loc[N];
-  // positions, and src (+ add) of the mesh at them (src2 the same, when TWO)
-  template <bool TWO>
-  __device__ __forceinline__ void init(const B& b, int c, const double* __restrict__ src, const double* __restrict__ src2,
-                                       double (&v)[N], double (&v2)[N]) {
-#pragma unroll
-    for (int t = 0; t < N; ++t) {
-      const int u = (int)threadIdx.x + t * NT;
-      const int r = div_small<EKH>(u), ri = div_small<EJ>(r);
-      const int i = LO + ri, j = LO + r - ri * EJ;
-      const int q = (i + j + c) & 1;                            // parity of the row's cells of this colour
-      const int k = LO + ((LO + q) & 1) + 2 * (u - r * EKH);    // first cell of that parity at or after LO
-      const bool in = CELLS % NT == 0 || u < CELLS;
-      const bool own = (unsigned)(i - OFF) < (unsigned)TI && (unsigned)(j - OFF) < (unsigned)TJ &&
-                       (unsigned)(k - OFF) < (unsigned)TK;
-      loc[t] = in ? ((i * B::RJ + j) * B::RKH + (k >> 1)) | (q ? kLocQ : 0) | (own ? kLocOwn : 0) : -1;
-      v[t] = 1.0;
-      v2[t] = 0.0;
-      if (in) {
-        const unsigned g = b.mesh(c, i, j, k);
-        v[t] = 1.0 + src[g];
-        if (TWO) v2[t] = src2[g];
-      }
-    }
-  }
-};
 
 // One half-sweep on a stage: new values of local colour c from the box in LDS, written back after
 // every thread has read. opd: 1 + delta of this thread's cells; f: their right-hand side, from LDS
@@ -147,21 +56,6 @@ __device__ __forceinline__ void half_sweep_box(const St& st, double* __restrict_
   __syncthreads();
 }
 
-// Sum of count values, in a fixed order, to every thread of the block.
-template <int NT>
-__device__ __forceinline__ double block_total(const double* __restrict__ p, int count, double (*red)[1]) {
-  double v[1] = {0.0};
-  for (int b = threadIdx.x; b < count; b += NT) v[0] += p[b];
-  v[0] = wave_sum_full(v[0]);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][0] = v[0];
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int w = 0; w < NT / 64; ++w) s += red[w][0];
-  __syncthreads();
-  return s;
-}
-
 template <int TI, int TJ, int TK, int NT, bool TAU>
 __global__ void __launch_bounds__(NT) blk_down_kernel(BlkDownArgs a) {
   constexpr int OFF = 5;
@@ -192,10 +86,10 @@ __global__ void __launch_bounds__(NT) blk_down_kernel(BlkDownArgs a) {
     }
   }
   double d4[s4.N], d3[s3.N], d2[s2.N], d1[s1.N], r4[s4.N], r3[s3.N], r2[s2.N], r1[s1.N];
-  s4.template init<TAU>(b, R, a.delta, a.rd, d4, r4);
-  s3.template init<TAU>(b, K, a.delta, a.rd, d3, r3);
-  s2.template init<false>(b, R, a.delta, nullptr, d2, r2);
-  s1.template init<false>(b, K, a.delta, nullptr, d1, r1);
+  s4.template init<TAU>(b, R, 1.0, a.delta, a.rd, d4, r4);
+  s3.template init<TAU>(b, K, 1.0, a.delta, a.rd, d3, r3);
+  s2.template init<false>(b, R, 1.0, a.delta, nullptr, d2, r2);
+  s1.template init<false>(b, K, 1.0, a.delta, nullptr, d1, r1);
   // the tile's cells for the defect: eight sons of a coarse cell on eight consecutive threads
   constexpr int TILE = TI * TJ * TK;
   static_assert(TILE <= NT && TILE % 64 == 0, "one cell of the tile per thread");
@@ -306,10 +200,10 @@ __global__ void __launch_bounds__(NT) blk_up_kernel(BlkUpArgs a) {
     ec[e] = a.theta_c[g] - a.that_c[g];
   }
   double d3[s3.N], d2[s2.N], d1[s1.N], d0[s0.N], f3[s3.N], f2[s2.N], f1[s1.N], f0[s0.N];
-  s3.template init<HAS_F>(b, R, a.delta, a.f, d3, f3);
-  s2.template init<HAS_F>(b, K, a.delta, a.f, d2, f2);
-  s1.template init<HAS_F>(b, R, a.delta, a.f, d1, f1);
-  s0.template init<HAS_F>(b, K, a.delta, a.f, d0, f0);
+  s3.template init<HAS_F>(b, R, 1.0, a.delta, a.f, d3, f3);
+  s2.template init<HAS_F>(b, K, 1.0, a.delta, a.f, d2, f2);
+  s1.template init<HAS_F>(b, R, 1.0, a.delta, a.f, d1, f1);
+  s0.template init<HAS_F>(b, K, 1.0, a.delta, a.f, d0, f0);
   const double C = block_total<NT>(a.c_part, a.c_count, red) * a.c_scale;   // ends in a barrier: ec is complete
   constexpr int NL = (2 * B::HALF + NT - 1) / NT;
 #pragma unroll
@@ -357,18 +251,6 @@ __global__ void __launch_bounds__(NT) blk_up_kernel(BlkUpArgs a) {
 // one wavefront, whose lanes exchange values through LDS without block barriers. As separate launches
 // (sweeps, right-hand side, defect, 20 coarsest sweeps with two block barriers a half-sweep,
 // transfers) the same work took about 140 us at 8^3.
-
-// Orders LDS accesses of the lanes of one wavefront (WAVE) or of the block.
-template <bool WAVE>
-__device__ __forceinline__ void tail_sync() {
-  if (WAVE) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
-}
 
 // A mesh of N^3 cells owned by W threads (a block, or the lanes of one wavefront): cell u + p W of each
 // colour belongs to thread u.
@@ -602,10 +484,7 @@ __global__ void __launch_bounds__(NT) blk_tail_kernel(BlkTailArgs a) {
 // block's time goes with its cells and their halo, so a smaller tile is faster while units are idle;
 // past that its larger halo costs more than it saves): 4^3 to 24^3, 4 x 4 x 8 at 32^3, 4 x 8 x 8 at
 // 40^3, 8^3 at 48^3, 8 x 8 x 16 at 64^3.
-struct BlkTile {
-  int ti, tj, tk;
-};
-static BlkTile blk_tile(int n) {
+BlkTile blk_tile(int n) {
   static const BlkTile tiles[] = {{4, 4, 4}, {4, 4, 8}, {4, 8, 8}, {8, 8, 8}, {8, 8, 16}};
   for (const BlkTile& t : tiles)
     if (n % t.ti == 0 && n % t.tj == 0 && n % t.tk == 0 && (n / t.ti) * (n / t.tj) * (n / t.tk) <= 256) return t;

@@ -128,6 +128,9 @@ struct Ctx {
                     int aa_depth = 0);
   int adj_sweep(int l);
   int adj_vcycle(int l, double* norm2);
+  int adj_blk_first() const;
+  int adj_blk_cycle(int l, double* r2);
+  bool tail_form(int t) const;
   double adj_last_norm = 0.0, adj_stop = 0.0;
   double* linsum(int l);
   int lin_sweep(int l, bool zero_start = false);

@@ -244,6 +244,10 @@ hipError_t launch_from_split(const double* split, double* natural, int n, const 
 // be null) receives (-sum b, 0).
 hipError_t launch_intake(const double* natural, double* split, int n, bool norm, double* seed, Reduce red,
                          hipStream_t s);
+// *result = sum of count partial sums, in a fixed order.
+hipError_t launch_finish(const double* partials, int count, double* result, hipStream_t s);
+// a -= (*sum) * scale; result[0] = sum of the squares of the result.
+hipError_t launch_center(double* a, size_t cells, const double* sum, double scale, Reduce red, hipStream_t s);
 // dst[0] = v0, dst[1] = v1 (count of them, 1 or 2)
 hipError_t launch_set_scalars(double* dst, double v0, double v1, int count, hipStream_t s);
 // result[0] = sum of a (size cells).

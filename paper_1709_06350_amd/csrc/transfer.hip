@@ -390,6 +390,21 @@ __global__ void __launch_bounds__(256) sum_kernel(const double* __restrict__ a, 
   block_partials<1>(v, partials);
 }
 
+// a -= sum * scale; partials: the squares of the result.
+__global__ void __launch_bounds__(256) center_kernel(double* __restrict__ a, size_t cells, const double* sum,
+                                                     double scale, double* __restrict__ partials) {
+  const double m = (*sum) * scale;
+  double s = 0.0;
+#pragma unroll 4
+  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < cells; e += (size_t)gridDim.x * blockDim.x) {
+    const double v = a[e] - m;
+    a[e] = v;
+    s += v * v;
+  }
+  double v[1] = {s};
+  block_partials<1>(v, partials);
+}
+
 __global__ void set_scalars_kernel(double* dst, double v0, double v1, int count) {
   if (threadIdx.x == 0) dst[0] = v0;
   if (threadIdx.x == 1 && count > 1) dst[1] = v1;
@@ -464,6 +479,18 @@ hipError_t launch_intake(const double* natural, double* split, int n, bool norm,
 hipError_t launch_sum(const double* a, size_t cells, Reduce red, hipStream_t s) {
   const int nb = stream_grid((cells + 255) / 256);
   hipLaunchKernelGGL(sum_kernel, dim3(nb), dim3(256), 0, s, a, cells, red.partials);
+  return finish_sums<1>(nb, red, nullptr, 0, s);
+}
+
+hipError_t launch_finish(const double* partials, int count, double* result, hipStream_t s) {
+  hipLaunchKernelGGL((finish_sums_kernel<1>), dim3(1), dim3(kFinishThreads), 0, s, partials, count, result,
+                     (double*)nullptr, 0);
+  return hipGetLastError();
+}
+
+hipError_t launch_center(double* a, size_t cells, const double* sum, double scale, Reduce red, hipStream_t s) {
+  const int nb = stream_grid((cells + 255) / 256);
+  hipLaunchKernelGGL(center_kernel, dim3(nb), dim3(256), 0, s, a, cells, sum, scale, red.partials);
   return finish_sums<1>(nb, red, nullptr, 0, s);
 }
 

@@ -172,7 +172,8 @@ int mr_schedule_candidates(const mr_ctx* ctx, int level, int* sched, int max_cou
 /* The FP32 sweep schedule of the mixed-precision form on a level (the tuner's choice, see the
  * persistent record of tuner choices below), in the (kind, tm, tj, nchunks) form of
  * mr_get_schedule; the first call allocates the context's mixed-precision buffers (and times the
- * candidates unless a recorded choice applies). Returns MR_EINVAL for a NULL argument or a level
+ * candidates unless a recorded choice applies). With the default two sweeps before and after, levels of
+ * 96 cells and fewer a side run several sweeps a launch instead. Returns MR_EINVAL for a NULL argument or a level
  * without a sweep (the coarsest), MR_ENOMEM if the buffers cannot be allocated. */
 int mr_get_lin_schedule(mr_ctx* ctx, int level, int sched[4]);
 

@@ -141,17 +141,7 @@ __global__ void __launch_bounds__(NT) adj_down_kernel(AdjDownArgs a) {
     adj_half_box<B, false, false>(b, s3, lam, K, r3, a.coef, h2, acc);
   } else {
     const double mu = block_total<NT>(a.mu.part, a.mu.count, reinterpret_cast<double(*)[1]>(red)) * a.mu.scale;
-    constexpr int NL = (2 * B::HALF + NT - 1) / NT;
-#pragma unroll
-    for (int t = 0; t < NL; ++t) {
-      const int e = tid + t * NT;
-      if (e < 2 * B::HALF) {
-        const int c = e >= B::HALF ? 1 : 0, r = e - c * B::HALF;
-        const int ij = div_small<B::RKH>(r), m = r - ij * B::RKH;
-        const int i = div_small<B::RJ>(ij), j = ij - i * B::RJ;
-        lam[e] = a.lam[b.mesh(c, i, j, 2 * m + ((i + j + c) & 1))] - mu;
-      }
-    }
+    for_box<B, NT>([&](int e, int c, int i, int j, int m, int q) { lam[e] = a.lam[b.mesh(c, i, j, 2 * m + q)] - mu; });
     __syncthreads();
     adj_half_box<B, true, false>(b, s4, lam, R, r4, a.coef, h2, acc);
     adj_half_box<B, true, false>(b, s3, lam, K, r3, a.coef, h2, acc);
@@ -229,22 +219,13 @@ __global__ void __launch_bounds__(NT) adj_up_kernel(AdjUpArgs a) {
   // the weights of the interpolation add up to one, so both offsets are one constant
   const double mu = block_total<NT>(a.mu.part, a.mu.count, red) * a.mu.scale +
                     block_total<NT>(a.mu_c.part, a.mu_c.count, red) * a.mu_c.scale;   // ends in a barrier: ec is complete
-  constexpr int NL = (2 * B::HALF + NT - 1) / NT;
-#pragma unroll
-  for (int t = 0; t < NL; ++t) {
-    const int e = tid + t * NT;
-    if (e < 2 * B::HALF) {
-      const int c = e >= B::HALF ? 1 : 0, r = e - c * B::HALF;
-      const int ij = div_small<B::RKH>(r), m = r - ij * B::RKH;
-      const int i = div_small<B::RJ>(ij), j = ij - i * B::RJ;
-      const int q = (i + j + c) & 1, k = 2 * m + q;
-      const double* __restrict__ p = ec + ((i >> 1) + 1) * (QJ * QK) + ((j >> 1) + 1) * QK + m + 1;
-      const int ni = (i & 1) ? QJ * QK : -QJ * QK, nj = (j & 1) ? QK : -QK, nk = q ? 1 : -1;
-      auto row = [&](int o) { return 0.75 * p[o] + 0.25 * p[o + nk]; };
-      const double corr = 0.75 * (0.75 * row(0) + 0.25 * row(nj)) + 0.25 * (0.75 * row(ni) + 0.25 * row(ni + nj));
-      lam[e] = a.lam[b.mesh(c, i, j, k)] + (corr - mu);
-    }
-  }
+  for_box<B, NT>([&](int e, int c, int i, int j, int m, int q) {
+    const double* __restrict__ p = ec + ((i >> 1) + 1) * (QJ * QK) + ((j >> 1) + 1) * QK + m + 1;
+    const int ni = (i & 1) ? QJ * QK : -QJ * QK, nj = (j & 1) ? QK : -QK, nk = q ? 1 : -1;
+    auto row = [&](int o) { return 0.75 * p[o] + 0.25 * p[o + nk]; };
+    const double corr = 0.75 * (0.75 * row(0) + 0.25 * row(nj)) + 0.25 * (0.75 * row(ni) + 0.25 * row(ni + nj));
+    lam[e] = a.lam[b.mesh(c, i, j, 2 * m + q)] + (corr - mu);
+  });
   __syncthreads();
   double acc = 0.0;
   adj_half_box<B, true, false>(b, s3, lam, R, r3, a.coef, a.h2, acc);

@@ -32,13 +32,14 @@ struct Box {
   }
   // 18 neighbours of the cell at position e of its colour's half (at[own colour], at[other colour]),
   // q its parity in z
-  static __device__ __forceinline__ void gather(const double* __restrict__ own, const double* __restrict__ other, int e,
-                                                int q, Nb18& t) {
+  template <typename T, typename Nb>
+  static __device__ __forceinline__ void gather(const T* __restrict__ own, const T* __restrict__ other, int e, int q,
+                                                Nb& t) {
     constexpr int DI = RJ * RKH, DJ = RKH;
-    const double* __restrict__ o = other + e;
-    const double* __restrict__ s = own + e;
-    const double* __restrict__ oq = o + q;   // column of k + 1; the one before it is that of k - 1
-    const double* __restrict__ sq = s + q;
+    const T* __restrict__ o = other + e;
+    const T* __restrict__ s = own + e;
+    const T* __restrict__ oq = o + q;   // column of k + 1; the one before it is that of k - 1
+    const T* __restrict__ sq = s + q;
     t.xm = o[-DI]; t.xp = o[DI];
     t.ym = o[-DJ]; t.yp = o[DJ];
     t.zm = oq[-1]; t.zp = oq[0];
@@ -64,6 +65,10 @@ __device__ __forceinline__ int div_small(int u) {
 // set inside the tile; -1 past the end. Worked out once per launch: formed again at every use the
 // divisions were a third of the half-sweeps' instructions.
 constexpr int kLocQ = 1 << 16, kLocOwn = 1 << 17, kLocPos = kLocQ - 1;
+template <typename T>
+struct Same {
+  using type = T;   // a parameter that takes its type from the others
+};
 template <class B, int TI, int TJ, int TK, int OFF, int S, int NT>
 struct Stage {
   static constexpr int EI = TI + 2 * S, EJ = TJ + 2 * S, EKH = (TK + 2 * S) / 2;
@@ -73,9 +78,9 @@ struct Stage {
   static_assert(N * NT < 8192 && B::HALF < kLocQ, "packed positions");
   int loc[N];
   // positions, and add + src of the mesh at them (and src2, when TWO)
-  template <bool TWO>
-  __device__ __forceinline__ void init(const B& b, int c, double add, const double* __restrict__ src,
-                                       const double* __restrict__ src2, double (&v)[N], double (&v2)[N]) {
+  template <bool TWO, typename T>
+  __device__ __forceinline__ void init(const B& b, int c, T add, const T* __restrict__ src,
+                                       const typename Same<T>::type* __restrict__ src2, T (&v)[N], T (&v2)[N]) {
 #pragma unroll
     for (int t = 0; t < N; ++t) {
       const int u = (int)threadIdx.x + t * NT;
@@ -88,7 +93,7 @@ struct Stage {
                        (unsigned)(k - OFF) < (unsigned)TK;
       loc[t] = in ? ((i * B::RJ + j) * B::RKH + (k >> 1)) | (q ? kLocQ : 0) | (own ? kLocOwn : 0) : -1;
       v[t] = add;
-      v2[t] = 0.0;
+      v2[t] = T(0);
       if (in) {
         const unsigned g = b.mesh(c, i, j, k);
         v[t] = add + src[g];
@@ -97,6 +102,23 @@ struct Stage {
     }
   }
 };
+
+// Calls f(e, c, i, j, m, q) for every cell of the box this thread loads: position e in the box, local
+// colour c, row (i, j), column m, parity q in z (k = 2 m + q).
+template <class B, int NT, class F>
+__device__ __forceinline__ void for_box(F f) {
+  constexpr int NL = (2 * B::HALF + NT - 1) / NT;
+#pragma unroll
+  for (int t = 0; t < NL; ++t) {
+    const int e = (int)threadIdx.x + t * NT;
+    if (e < 2 * B::HALF) {
+      const int c = e >= B::HALF ? 1 : 0, r = e - c * B::HALF;
+      const int ij = div_small<B::RKH>(r), m = r - ij * B::RKH;
+      const int i = div_small<B::RJ>(ij), j = ij - i * B::RJ;
+      f(e, c, i, j, m, (i + j + c) & 1);
+    }
+  }
+}
 
 // Sum of count values, in a fixed order, to every thread of the block.
 template <int NT>

@@ -74,17 +74,7 @@ __global__ void __launch_bounds__(NT) blk_down_kernel(BlkDownArgs a) {
 
   // every global load of the launch is issued here: theta of the box, delta of each stage's cells,
   // the partial sums of the shift
-  constexpr int NL = (2 * B::HALF + NT - 1) / NT;
-#pragma unroll
-  for (int t = 0; t < NL; ++t) {
-    const int e = tid + t * NT;
-    if (e < 2 * B::HALF) {
-      const int c = e >= B::HALF ? 1 : 0, r = e - c * B::HALF;
-      const int ij = div_small<B::RKH>(r), m = r - ij * B::RKH;
-      const int i = div_small<B::RJ>(ij), j = ij - i * B::RJ;
-      th[e] = a.theta[b.mesh(c, i, j, 2 * m + ((i + j + c) & 1))];
-    }
-  }
+  for_box<B, NT>([&](int e, int c, int i, int j, int m, int q) { th[e] = a.theta[b.mesh(c, i, j, 2 * m + q)]; });
   double d4[s4.N], d3[s3.N], d2[s2.N], d1[s1.N], r4[s4.N], r3[s3.N], r2[s2.N], r1[s1.N];
   s4.template init<TAU>(b, R, 1.0, a.delta, a.rd, d4, r4);
   s3.template init<TAU>(b, K, 1.0, a.delta, a.rd, d3, r3);
@@ -205,23 +195,14 @@ __global__ void __launch_bounds__(NT) blk_up_kernel(BlkUpArgs a) {
   s1.template init<HAS_F>(b, R, 1.0, a.delta, a.f, d1, f1);
   s0.template init<HAS_F>(b, K, 1.0, a.delta, a.f, d0, f0);
   const double C = block_total<NT>(a.c_part, a.c_count, red) * a.c_scale;   // ends in a barrier: ec is complete
-  constexpr int NL = (2 * B::HALF + NT - 1) / NT;
-#pragma unroll
-  for (int t = 0; t < NL; ++t) {
-    const int e = tid + t * NT;
-    if (e < 2 * B::HALF) {
-      const int c = e >= B::HALF ? 1 : 0, r = e - c * B::HALF;
-      const int ij = div_small<B::RKH>(r), m = r - ij * B::RKH;
-      const int i = div_small<B::RJ>(ij), j = ij - i * B::RJ;
-      const int q = (i + j + c) & 1, k = 2 * m + q;
-      // parent's position in ec and the neighbour towards the fine cell
-      const double* __restrict__ p = ec + ((i >> 1) + 1) * (QJ * QK) + ((j >> 1) + 1) * QK + m + 1;
-      const int ni = (i & 1) ? QJ * QK : -QJ * QK, nj = (j & 1) ? QK : -QK, nk = q ? 1 : -1;
-      auto row = [&](int o) { return 0.75 * p[o] + 0.25 * p[o + nk]; };
-      const double corr = 0.75 * (0.75 * row(0) + 0.25 * row(nj)) + 0.25 * (0.75 * row(ni) + 0.25 * row(ni + nj));
-      th[e] = a.theta[b.mesh(c, i, j, k)] + corr;
-    }
-  }
+  for_box<B, NT>([&](int e, int c, int i, int j, int m, int q) {
+    // parent's position in ec and the neighbour towards the fine cell
+    const double* __restrict__ p = ec + ((i >> 1) + 1) * (QJ * QK) + ((j >> 1) + 1) * QK + m + 1;
+    const int ni = (i & 1) ? QJ * QK : -QJ * QK, nj = (j & 1) ? QK : -QK, nk = q ? 1 : -1;
+    auto row = [&](int o) { return 0.75 * p[o] + 0.25 * p[o + nk]; };
+    const double corr = 0.75 * (0.75 * row(0) + 0.25 * row(nj)) + 0.25 * (0.75 * row(ni) + 0.25 * row(ni + nj));
+    th[e] = a.theta[b.mesh(c, i, j, 2 * m + q)] + corr;
+  });
   __syncthreads();
   const double h2 = a.h2, ih2 = a.ih2;
   constexpr int FM = HAS_F ? kRegF : kNoF;

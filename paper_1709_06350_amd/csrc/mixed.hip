@@ -25,6 +25,8 @@
 #include "mr_ctx.h"
 #include "mr_device.h"
 #include "mr_kernels.h"
+#include "lin_block.h"
+#include "lin_block_launch.h"
 #include "mixed_device.h"
 #include "tuning.h"
 
@@ -625,6 +627,7 @@ struct LinLevel {
   bool fused = false;    // the one-launch sweep (schedule fz) won the tuner
   LinFusedCfg fz;
   int rr_tm = 0, rr_tj = 0, rr_nch = 0;   // timed defect + restriction tile (rr_tm == 0: default)
+  double* part = nullptr;   // block form: sums of the down launch, of its coarse rhs, of the up launch
 };
 
 // Krylov space of the inner solve on the finest mesh: V[0..m] orthonormal mean-free vectors,
@@ -646,7 +649,7 @@ struct CoarseGraph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   std::vector<int> cur_in, cur_out;
-  int npre = -1, npost = -1, ncoarse = -1;
+  int npre = -1, npost = -1, ncoarse = -1, flags = 0;
 };
 
 struct MixedState {
@@ -893,6 +896,11 @@ static int mixed_alloc(Ctx* c) {
       if (e != hipSuccess) return fail(MR_ENOMEM, "mixed precision buffers: %s", hipGetErrorString(e));
       m->owned.push_back(*b);
     }
+    if (lin_blk_blocks(c->lv[l].n) > 0) {
+      hipError_t e = hipMalloc((void**)&L.part, 3 * kLinBlkMaxBlocks * sizeof(double));
+      if (e != hipSuccess) return fail(MR_ENOMEM, "mixed precision buffers: %s", hipGetErrorString(e));
+      m->owned.push_back(L.part);
+    }
   }
   // linear sweep schedule per level, timed on the level's buffers
   for (int l = 0; l + 1 < c->nlev; ++l) {
@@ -1038,12 +1046,95 @@ int Ctx::lin_sweep(int l, bool zero_start) {
   return MR_OK;
 }
 
+// First level of the block form of the linear cycle (lin_block.h; nlev: none): the default cycle of two
+// sweeps before and after on small levels only. The finest level keeps its timed sweeps while the caller
+// times them.
+int Ctx::lin_blk_first() const {
+  if ((opts.flags & MR_FLAG_TWO_PASS) || opts.npre != 2 || opts.npost != 2) return nlev;
+  int t = 0;
+  while (t < nlev && lv[t].n > 12) ++t;
+  if (t == 0 || t >= nlev || !tail_form(t)) return nlev;
+  const int lowest = timer.on ? 1 : 0;
+  while (t > lowest && mixed->lv[t - 1].part) --t;
+  return t;
+}
+
+// The cycle of level l in the block form: from e = 0, or (zero false) from e[cur]; the result is e[cur], and
+// a level other than the tail's ends in the buffer it began in. c: sums of the level's right-hand side, or
+// of the last up launch.
+int Ctx::lin_blk_cycle(int l, bool zero, const double* c_part, int c_count) {
+  LinLevel& L = mixed->lv[l];
+  Level& F = lv[l];
+  const LinShift c{c_part, c_count, 1.0 / (double)F.cells};
+  const float h2 = (float)(F.h * F.h);
+  hipError_t e;
+  if (F.n <= 12) {
+    const bool coarsest = l == nlev - 1;
+    LinTail2Args a{};
+    a.rhs = L.rhs;
+    a.base = L.base;
+    a.sb = L.sb;
+    a.base_c = coarsest ? nullptr : mixed->lv[l + 1].base;
+    a.sb_c = coarsest ? nullptr : mixed->lv[l + 1].sb;
+    a.bq = scal + kSlotBase;
+    a.n = F.n;
+    a.npre = opts.npre;
+    a.npost = opts.npost;
+    a.ncoarse = opts.ncoarse;
+    a.h2 = h2;
+    a.c = c;
+    a.e_out = L.e[L.cur];
+    e = launch_lin_tail2(a, stream);
+    return e == hipSuccess ? MR_OK : hip_fail(e, "linear block tail");
+  }
+  LinLevel& Lc = mixed->lv[l + 1];
+  const int nb = lin_blk_blocks(F.n);
+  LinDownArgs d{};
+  d.e = zero ? nullptr : L.e[L.cur];
+  d.rhs = L.rhs;
+  d.base = L.base;
+  d.sb = L.sb;
+  d.bq = scal + kSlotBase;
+  d.n = F.n;
+  d.h2 = h2;
+  d.ih2 = (float)(1.0 / (F.h * F.h));
+  d.c = c;
+  L.cur ^= 1;
+  d.e_out = L.e[L.cur];
+  d.rhs_c = Lc.rhs;
+  d.part_c = L.part;
+  d.part_r = L.part + kLinBlkMaxBlocks;
+  if ((e = launch_lin_down(d, stream)) != hipSuccess) return hip_fail(e, "linear block down");
+  int rc = lin_blk_cycle(l + 1, true, d.part_r, nb);
+  if (rc != MR_OK) return rc;
+  LinUpArgs u{};
+  u.e = L.e[L.cur];
+  u.e_c = Lc.e[Lc.cur];
+  u.rhs = L.rhs;
+  u.base = L.base;
+  u.sb = L.sb;
+  u.bq = d.bq;
+  u.n = F.n;
+  u.h2 = h2;
+  u.ih2 = d.ih2;
+  u.c = LinShift{d.part_c, nb, c.scale};
+  L.cur ^= 1;
+  u.e_out = L.e[L.cur];
+  u.part_c = L.part + 2 * kLinBlkMaxBlocks;
+  e = launch_lin_up(u, stream);
+  return e == hipSuccess ? MR_OK : hip_fail(e, "linear block up");
+}
+
 // Linear V-cycle on level l; zero: e of the level is zero on entry (it is then not read: the first
 // pre-smoothing sweep starts from zero, or the coarsest level is cleared first).
 int Ctx::lin_vcycle(int l, bool zero) {
   LinLevel& L = mixed->lv[l];
   Level& F = lv[l];
   hipError_t e;
+  if (l >= lin_blk_first() && (zero || l == 0)) {
+    if (zero) return lin_blk_cycle(l, true, linsum(l), 2);
+    return lin_blk_cycle(l, false, L.part + 2 * kLinBlkMaxBlocks, lin_blk_blocks(F.n));
+  }
   if (l > 0 && zero && F.n <= kTailMaxN && nlev - l <= kTailMaxLev) {
     // this level and all coarser ones in one workgroup
     LinTailArgs a{};
@@ -1096,7 +1187,7 @@ int Ctx::lin_vcycle(int l, bool zero) {
 int Ctx::lin_coarse_cycle() {
   CoarseGraph& g = mixed->cg;
   hipError_t e = hipSuccess;
-  if (!g.exec || g.npre != opts.npre || g.npost != opts.npost || g.ncoarse != opts.ncoarse) {
+  if (!g.exec || g.npre != opts.npre || g.npost != opts.npost || g.ncoarse != opts.ncoarse || g.flags != opts.flags) {
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
     if (g.graph) (void)hipGraphDestroy(g.graph);
     g.exec = nullptr;
@@ -1118,6 +1209,7 @@ int Ctx::lin_coarse_cycle() {
     g.npre = opts.npre;
     g.npost = opts.npost;
     g.ncoarse = opts.ncoarse;
+    g.flags = opts.flags;
   }
   for (int l = 1; l < nlev; ++l) mixed->lv[l].cur = g.cur_in[l];
   if ((e = hipGraphLaunch(g.exec, stream)) != hipSuccess) return hip_fail(e, "graph launch");

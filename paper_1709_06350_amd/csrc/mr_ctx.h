@@ -135,6 +135,8 @@ struct Ctx {
   double* linsum(int l);
   int lin_sweep(int l, bool zero_start = false);
   int lin_vcycle(int l, bool zero = false);
+  int lin_blk_first() const;
+  int lin_blk_cycle(int l, bool zero, const double* c_part, int c_count);
   int lin_coarse_cycle();
   int mixed_ready();
   int lin_schedule(int l, int sched[4]);

@@ -141,7 +141,8 @@ __global__ void __launch_bounds__(NT) adj_down_kernel(AdjDownArgs a) {
     adj_half_box<B, false, false>(b, s3, lam, K, r3, a.coef, h2, acc);
   } else {
     const double mu = block_total<NT>(a.mu.part, a.mu.count, reinterpret_cast<double(*)[1]>(red)) * a.mu.scale;
-    for_box<B, NT>([&](int e, int c, int i, int j, int m, int q) { lam[e] = a.lam[b.mesh(c, i, j, 2 * m + q)] - mu; });
+    const Field<double> lam_in(a.lam, a.n);
+    for_box<double, B, NT>(b, [&](int e, unsigned o, int i, int j, int m, int q) { lam[e] = lam_in[o] - mu; });
     __syncthreads();
     adj_half_box<B, true, false>(b, s4, lam, R, r4, a.coef, h2, acc);
     adj_half_box<B, true, false>(b, s3, lam, K, r3, a.coef, h2, acc);
@@ -219,12 +220,13 @@ __global__ void __launch_bounds__(NT) adj_up_kernel(AdjUpArgs a) {
   // the weights of the interpolation add up to one, so both offsets are one constant
   const double mu = block_total<NT>(a.mu.part, a.mu.count, red) * a.mu.scale +
                     block_total<NT>(a.mu_c.part, a.mu_c.count, red) * a.mu_c.scale;   // ends in a barrier: ec is complete
-  for_box<B, NT>([&](int e, int c, int i, int j, int m, int q) {
+  const Field<double> lam_in(a.lam, a.n);
+  for_box<double, B, NT>(b, [&](int e, unsigned o, int i, int j, int m, int q) {
     const double* __restrict__ p = ec + ((i >> 1) + 1) * (QJ * QK) + ((j >> 1) + 1) * QK + m + 1;
     const int ni = (i & 1) ? QJ * QK : -QJ * QK, nj = (j & 1) ? QK : -QK, nk = q ? 1 : -1;
-    auto row = [&](int o) { return 0.75 * p[o] + 0.25 * p[o + nk]; };
+    auto row = [&](int s) { return 0.75 * p[s] + 0.25 * p[s + nk]; };
     const double corr = 0.75 * (0.75 * row(0) + 0.25 * row(nj)) + 0.25 * (0.75 * row(ni) + 0.25 * row(ni + nj));
-    lam[e] = a.lam[b.mesh(c, i, j, 2 * m + q)] + (corr - mu);
+    lam[e] = lam_in[o] + (corr - mu);
   });
   __syncthreads();
   double acc = 0.0;
@@ -440,7 +442,7 @@ __global__ void __launch_bounds__(NT) adj_tail_kernel(AdjTailArgs a) {
           const int q = (i + j + c) & 1;
           const double* __restrict__ x = ec + (((i >> 1) + 1) * (NB + 2) + (j >> 1) + 1) * (NB + 2) + m + 1;
           const int ni = ((i & 1) ? 1 : -1) * (NB + 2) * (NB + 2), nj = ((j & 1) ? 1 : -1) * (NB + 2), nk = q ? 1 : -1;
-          auto row = [&](int o) { return 0.75 * x[o] + 0.25 * x[o + nk]; };
+          auto row = [&](int s) { return 0.75 * x[s] + 0.25 * x[s + nk]; };
           A.put(c, p, A.get(c, p) + 0.75 * (0.75 * row(0) + 0.25 * row(nj)) + 0.25 * (0.75 * row(ni) + 0.25 * row(ni + nj)));
         }
     __syncthreads();

@@ -24,12 +24,14 @@
 #include "mr_ctx.h"
 #include "mr_device.h"
 #include "mr_kernels.h"
+#include "lin_block.h"
 #include "mixed_device.h"
 #include "tuning.h"
 
 namespace mr {
 
 constexpr int kBoxPartials = 4096;   // partial-sum slots per box (x kMaxNV values)
+constexpr int kBatchBlkMax = 256;    // blocks of a box's launch in the block form
 
 struct BLevel {
   float* e[2];
@@ -38,6 +40,8 @@ struct BLevel {
   float* sb;
   const double* delta;
   double* lsum;     // 3 doubles: inner running sums of this level
+  double* part;     // block form (levels of 64^3 and below): sums of the down launch, of its coarse
+                    // right-hand side, of the up launch (kBatchBlkMax each)
 };
 
 // Convergence state of one box, written by the last block of its residual reduction.
@@ -169,7 +173,111 @@ __global__ void b_inner_shift_kernel(const BBox* boxes, const int* cls, int nb) 
   x.lv[0].lsum[1] = 0.0;
 }
 
-template <int TM, int TJ, int COL>
+// Red half of a sweep from e = 0 (lin_red_zero_kernel of mixed.hip, a share of a box per block): e_red =
+// -h^2 (rhs_red - C) / 6 and the sum of rhs_red; e needs no clearing.
+__global__ void __launch_bounds__(1024) b_red_zero_kernel(const BBox* boxes, const int* cls, int bpb, int l, int cur,
+                                                          size_t cells, float h2) {
+  int b, t;
+  if (!box_of(boxes, cls, bpb, b, t)) return;
+  const BBox& x = boxes[b];
+  const BLevel& L = x.lv[l];
+  const float C = (float)((L.lsum[0] + L.lsum[1]) / (double)cells);
+  const float g = -h2 * (1.0f / 6.0f);
+  double acc = 0.0;
+  const size_t half = cells / 2;
+  for (size_t e = t * (size_t)blockDim.x + threadIdx.x; e < half; e += (size_t)bpb * blockDim.x) {
+    const float r = L.rhs[e];
+    L.e[cur ^ 1][e] = g * (r - C);
+    acc += (double)r;
+  }
+  double v[1] = {acc};
+  grid_sum<1>(v, x.partials, x.counter, L.lsum + 2, bpb, t);
+}
+
+// Block form of the linear cycle (lin_block.h), a tile of a box per block. from: where the shift's sums
+// are -- the level's running sums, the finer level's down launch (nfrom blocks), or the level's own up
+// launch.
+enum { kFromSums = 0, kFromFiner = 1, kFromUp = 2 };
+__device__ __forceinline__ LinShift box_shift(const BBox& x, int l, int from, int nfrom, double scale) {
+  const double* p = from == kFromSums ? x.lv[l].lsum
+                                      : (from == kFromFiner ? x.lv[l - 1].part + kBatchBlkMax : x.lv[l].part + 2 * kBatchBlkMax);
+  return LinShift{p, from == kFromSums ? 2 : nfrom, scale};
+}
+
+template <int TI, int TJ, int TK, int NT, bool ZERO>
+__global__ void __launch_bounds__(NT) b_lin_down_kernel(const BBox* boxes, const int* cls, int bpb, int l, int cur, int n,
+                                                        float h2, float ih2, int from, int nfrom) {
+  __shared__ LinBoxLds<TI, TJ, TK, ZERO ? 4 : 5> sh;
+  int b, t;
+  if (!box_of(boxes, cls, bpb, b, t)) return;
+  const BBox& x = boxes[b];
+  const BLevel& L = x.lv[l];
+  LinDownArgs a{};
+  a.e = L.e[cur];
+  a.rhs = L.rhs;
+  a.base = L.base;
+  a.sb = L.sb;
+  a.bq = x.res + 5;
+  a.n = n;
+  a.h2 = h2;
+  a.ih2 = ih2;
+  a.c = box_shift(x, l, from, nfrom, 1.0 / ((double)n * n * n));
+  a.e_out = L.e[cur ^ 1];
+  a.rhs_c = x.lv[l + 1].rhs;
+  a.part_c = L.part;
+  a.part_r = L.part + kBatchBlkMax;
+  lin_down_body<TI, TJ, TK, NT, ZERO>(a, t, t, sh);
+}
+
+template <int TI, int TJ, int TK, int NT>
+__global__ void __launch_bounds__(NT) b_lin_up_kernel(const BBox* boxes, const int* cls, int bpb, int l, int cur, int cur_c,
+                                                      int n, float h2, float ih2) {
+  __shared__ LinBoxLds<TI, TJ, TK, 4> sh;
+  int b, t;
+  if (!box_of(boxes, cls, bpb, b, t)) return;
+  const BBox& x = boxes[b];
+  const BLevel& L = x.lv[l];
+  LinUpArgs a{};
+  a.e = L.e[cur];
+  a.e_c = x.lv[l + 1].e[cur_c];
+  a.rhs = L.rhs;
+  a.base = L.base;
+  a.sb = L.sb;
+  a.bq = x.res + 5;
+  a.n = n;
+  a.h2 = h2;
+  a.ih2 = ih2;
+  a.c = LinShift{L.part, bpb, 1.0 / ((double)n * n * n)};
+  a.e_out = L.e[cur ^ 1];
+  a.part_c = L.part + 2 * kBatchBlkMax;
+  lin_up_body<TI, TJ, TK, NT>(a, t, t, sh);
+}
+
+template <int NA, int NB, int NT>
+__global__ void __launch_bounds__(NT) b_lin_tail_kernel(const BBox* boxes, const int* cls, int l, int npre, int npost,
+                                                        int ncoarse, float h2, int from, int nfrom) {
+  __shared__ LinTail2Lds<NA, NB> sh;
+  const BBox& x = boxes[cls[blockIdx.x]];
+  if (!x.st->active) return;
+  const BLevel& L = x.lv[l];
+  LinTail2Args a{};
+  a.rhs = L.rhs;
+  a.base = L.base;
+  a.sb = L.sb;
+  a.base_c = x.lv[l + 1].base;
+  a.sb_c = x.lv[l + 1].sb;
+  a.bq = x.res + 5;
+  a.n = NA;
+  a.npre = npre;
+  a.npost = npost;
+  a.ncoarse = ncoarse;
+  a.h2 = h2;
+  a.c = box_shift(x, l, from, nfrom, 1.0 / ((double)NA * NA * NA));
+  a.e_out = L.e[0];
+  lin_tail2_body<NA, NB, NT>(a, sh);
+}
+
+template <int TM, int TJ, int COL, bool ZB = false>
 __global__ void __launch_bounds__(TM * TJ) b_lin_sweep_kernel(const BBox* boxes, const int* cls, int bpb, int l, int cur,
                                                               int n, float h2, float ih2, int tiles_j, int tiles_m,
                                                               int ci) {
@@ -200,7 +308,7 @@ __global__ void __launch_bounds__(TM * TJ) b_lin_sweep_kernel(const BBox* boxes,
   a.tiles_j = tiles_j;
   a.tiles_m = tiles_m;
   a.ci = ci;
-  lin_sweep_pipe_body<TM, TJ, COL>(a, t, t, bpb, lds);
+  lin_sweep_pipe_body<TM, TJ, COL, ZB>(a, t, t, bpb, lds);
 }
 
 __global__ void __launch_bounds__(256) b_resid_restrict_kernel(const BBox* boxes, const int* cls, int bpb, int l, int cur,
@@ -387,7 +495,7 @@ __global__ void __launch_bounds__(256) b_aa_combine_kernel(const BBox* boxes, co
 #define MR_BRT_TILES(X) X(64, 8) X(32, 8) X(16, 8) X(8, 8) X(4, 8)
 
 static hipError_t launch_b_lin_sweep(const BBox* boxes, const int* cls, int nb, const TileCfg& t, int l, int colour, int cur,
-                                     int n, double h, hipStream_t s) {
+                                     int n, double h, hipStream_t s, bool zero_black = false) {
   const int bpb = t.tiles_j * t.tiles_m * (n / t.ci);
   if (t.ci % 4 != 0) return hipErrorInvalidValue;
   const float h2 = (float)(h * h), ih2 = (float)(1.0 / (h * h));
@@ -396,6 +504,9 @@ static hipError_t launch_b_lin_sweep(const BBox* boxes, const int* cls, int nb, 
     if (colour == 0)                                                                                             \
       hipLaunchKernelGGL((b_lin_sweep_kernel<TM, TJ, 0>), dim3(nb * bpb), dim3(TM * TJ), 0, s, boxes, cls, bpb, l, \
                          cur, n, h2, ih2, t.tiles_j, t.tiles_m, t.ci);                                           \
+    else if (zero_black)                                                                                         \
+      hipLaunchKernelGGL((b_lin_sweep_kernel<TM, TJ, 1, true>), dim3(nb * bpb), dim3(TM * TJ), 0, s, boxes, cls,  \
+                         bpb, l, cur, n, h2, ih2, t.tiles_j, t.tiles_m, t.ci);                                   \
     else                                                                                                         \
       hipLaunchKernelGGL((b_lin_sweep_kernel<TM, TJ, 1>), dim3(nb * bpb), dim3(TM * TJ), 0, s, boxes, cls, bpb, l, \
                          cur, n, h2, ih2, t.tiles_j, t.tiles_m, t.ci);                                           \
@@ -651,6 +762,75 @@ int rows_grid_b(int rows) { return rows < 1024 ? rows : 1024; }
 
 }  // namespace
 
+// Tile of a level in the block form, a fixed function of its size (0: the plain launches): boxes fill the
+// chip together, so the tiles are the larger ones, whose halo is a smaller share of the work. At 48^3
+// down and up of 21 boxes take 228 us (the plain launches about 320). At 64^3 the two sides meet: a batch
+// of 64 boxes of 64^3-128^3 takes 133.0 ms with the form at 64^3 and 127.2 without, 8 boxes 31.5 and 39.1,
+// 2 boxes 11.4 and 15.8; the form ends there.
+static BlkTile batch_blk_tile(int n) {
+  if (n == 64) return BlkTile{8, 8, 16};
+  if (n >= 24 && n <= 48 && n % 8 == 0) return BlkTile{8, 8, 8};
+  if (n == 16) return BlkTile{4, 4, 8};
+  return BlkTile{0, 0, 0};
+}
+#define MR_BB_TILES(X) X(4, 4, 8, 512) X(8, 8, 8, 512) X(8, 8, 16, 1024)
+
+// First level of a class in the block form (nlev: none).
+static int batch_blk_first(const SizeClass& c, const mr_opts& o) {
+  if (o.npre != 2 || o.npost != 2) return c.nlev;
+  int t = 0;
+  while (t < c.nlev && c.ns[t] > 12) ++t;
+  if (t == 0 || t >= c.nlev) return c.nlev;
+  if ((c.ns[t] != 8 && c.ns[t] != 12) || t != c.nlev - 2) return c.nlev;   // tails: 8^3 over 4^3, 12^3 over 6^3
+  while (t > 0 && batch_blk_tile(c.ns[t - 1]).ti != 0) --t;
+  return t;
+}
+
+// The cycle of level l and below in the block form, from e[cur] (zero: from e = 0) back into e[cur].
+static hipError_t record_block(const SizeClass& c, BBox* dboxes, const mr_opts& o, int l, std::vector<int>& cur, bool zero,
+                               int from, int nfrom, hipStream_t s) {
+  const int nb = (int)c.boxes.size(), n = c.ns[l];
+  const float h2 = (float)(c.hs[l] * c.hs[l]), ih2 = (float)(1.0 / (c.hs[l] * c.hs[l]));
+  if (n <= 12) {
+    cur[l] = 0;
+#define MR_BB_TAIL(NA, NB, NT)                                                                                      \
+    if (n == NA)                                                                                                    \
+      hipLaunchKernelGGL((b_lin_tail_kernel<NA, NB, NT>), dim3(nb), dim3(NT), 0, s, dboxes, c.d_boxes, l, o.npre, \
+                         o.npost, o.ncoarse, h2, from, nfrom);
+    MR_BB_TAIL(8, 4, 256)
+    MR_BB_TAIL(12, 6, 896)
+#undef MR_BB_TAIL
+    return hipGetLastError();
+  }
+  const BlkTile t = batch_blk_tile(n);
+  const int bpb = (n / t.ti) * (n / t.tj) * (n / t.tk);
+  if (bpb > kBatchBlkMax) return hipErrorInvalidValue;
+#define MR_BB_DOWN(TI, TJ, TK, NT)                                                                                      \
+  if (t.ti == TI && t.tj == TJ && t.tk == TK) {                                                                         \
+    if (zero)                                                                                                           \
+      hipLaunchKernelGGL((b_lin_down_kernel<TI, TJ, TK, NT, true>), dim3(nb * bpb), dim3(NT), 0, s, dboxes, c.d_boxes,  \
+                         bpb, l, cur[l], n, h2, ih2, from, nfrom);                                                      \
+    else                                                                                                                \
+      hipLaunchKernelGGL((b_lin_down_kernel<TI, TJ, TK, NT, false>), dim3(nb * bpb), dim3(NT), 0, s, dboxes, c.d_boxes, \
+                         bpb, l, cur[l], n, h2, ih2, from, nfrom);                                                      \
+  }
+  MR_BB_TILES(MR_BB_DOWN)
+#undef MR_BB_DOWN
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  cur[l] ^= 1;
+  cur[l + 1] = 0;
+  if ((e = record_block(c, dboxes, o, l + 1, cur, true, kFromFiner, bpb, s)) != hipSuccess) return e;
+#define MR_BB_UP(TI, TJ, TK, NT)                                                                                     \
+  if (t.ti == TI && t.tj == TJ && t.tk == TK)                                                                        \
+    hipLaunchKernelGGL((b_lin_up_kernel<TI, TJ, TK, NT>), dim3(nb * bpb), dim3(NT), 0, s, dboxes, c.d_boxes, bpb, l, \
+                       cur[l], cur[l + 1], n, h2, ih2);
+  MR_BB_TILES(MR_BB_UP)
+#undef MR_BB_UP
+  cur[l] ^= 1;
+  return hipGetLastError();
+}
+
 static int record_iteration(std::vector<SizeClass>& cls, BBox* dboxes, const mr_opts& o, hipStream_t s) {
   hipError_t e = hipSuccess;
   auto ok = [&]() { return e == hipSuccess ? (e = hipGetLastError()) == hipSuccess : false; };
@@ -694,7 +874,7 @@ static int record_iteration(std::vector<SizeClass>& cls, BBox* dboxes, const mr_
   for (auto& c : cls) {
     const int nb = (int)c.boxes.size();
     const size_t cells = (size_t)c.n * c.n * c.n;
-    hipLaunchKernelGGL(b_fill_kernel, dim3(nb * 64), dim3(256), 0, s, dboxes, c.d_boxes, 64, 0, 0, cells);
+    if (o.npre == 0) hipLaunchKernelGGL(b_fill_kernel, dim3(nb * 64), dim3(256), 0, s, dboxes, c.d_boxes, 64, 0, 0, cells);
     hipLaunchKernelGGL(b_inner_shift_kernel, dim3((nb + 63) / 64), dim3(64), 0, s, dboxes, c.d_boxes, nb);
     if (!ok()) return hip_fail(e, "batched inner start");
   }
@@ -707,15 +887,35 @@ static int record_iteration(std::vector<SizeClass>& cls, BBox* dboxes, const mr_
         if (l >= c.nlev) continue;
         const int n = c.ns[l];
         const double h = c.hs[l];
+        const int first = batch_blk_first(c, o);
+        const bool zero = l > 0 || k == 0;   // the level starts from e = 0
+        if (l >= first) {
+          if (l > first) continue;
+          e = record_block(c, dboxes, o, l, cur[ci], zero, zero ? kFromSums : kFromUp,
+                           zero ? 2 : (n / batch_blk_tile(n).ti) * (n / batch_blk_tile(n).tj) * (n / batch_blk_tile(n).tk), s);
+          if (e != hipSuccess) return hip_fail(e, "batched block cycle");
+          continue;
+        }
         if (l == c.nlev - 1) {
+          const size_t cells = (size_t)n * n * n;
+          hipLaunchKernelGGL(b_fill_kernel, dim3(nb), dim3(256), 0, s, dboxes, c.d_boxes, 1, l, cur[ci][l], cells);
           hipLaunchKernelGGL(b_coarsest_kernel, dim3(nb), dim3(256), sizeof(LinCoarsestShared), s, dboxes, c.d_boxes, l,
                              cur[ci][l], n, o.ncoarse, (float)(h * h), (float)(1.0 / (h * h)));
           if (!ok()) return hip_fail(e, "batched coarsest");
           continue;
         }
         for (int sw = 0; sw < o.npre; ++sw) {
-          e = launch_b_lin_sweep(dboxes, c.d_boxes, nb, c.tiles[l], l, 0, cur[ci][l], n, h, s);
-          if (e == hipSuccess) e = launch_b_lin_sweep(dboxes, c.d_boxes, nb, c.tiles[l], l, 1, cur[ci][l], n, h, s);
+          const bool from_zero = zero && sw == 0;
+          if (from_zero) {
+            const size_t cells = (size_t)n * n * n;
+            const int bpb = (int)std::max<size_t>(1, std::min<size_t>(32, cells / 2 / 16384));
+            hipLaunchKernelGGL(b_red_zero_kernel, dim3(nb * bpb), dim3(1024), 0, s, dboxes, c.d_boxes, bpb, l, cur[ci][l],
+                               cells, (float)(h * h));
+            e = hipGetLastError();
+          } else {
+            e = launch_b_lin_sweep(dboxes, c.d_boxes, nb, c.tiles[l], l, 0, cur[ci][l], n, h, s);
+          }
+          if (e == hipSuccess) e = launch_b_lin_sweep(dboxes, c.d_boxes, nb, c.tiles[l], l, 1, cur[ci][l], n, h, s, from_zero);
           if (e != hipSuccess) return hip_fail(e, "batched sweep");
           cur[ci][l] ^= 1;
         }
@@ -737,7 +937,7 @@ static int record_iteration(std::vector<SizeClass>& cls, BBox* dboxes, const mr_
         }
         cur[ci][l + 1] = 0;
         const size_t cc = (size_t)m * m * m;
-        hipLaunchKernelGGL(b_fill_kernel, dim3(nb * 64), dim3(256), 0, s, dboxes, c.d_boxes, 64, l + 1, 0, cc);
+        if (o.npre == 0) hipLaunchKernelGGL(b_fill_kernel, dim3(nb * 64), dim3(256), 0, s, dboxes, c.d_boxes, 64, l + 1, 0, cc);
         if (!ok()) return hip_fail(e, "batched restriction");
       }
     }
@@ -746,7 +946,7 @@ static int record_iteration(std::vector<SizeClass>& cls, BBox* dboxes, const mr_
       for (size_t ci = 0; ci < cls.size(); ++ci) {
         SizeClass& c = cls[ci];
         const int nb = (int)c.boxes.size();
-        if (l >= c.nlev - 1) continue;
+        if (l >= c.nlev - 1 || l >= batch_blk_first(c, o)) continue;
         const int n = c.ns[l];
         const double h = c.hs[l];
         if (prolong_rows_ok(n)) {
@@ -893,6 +1093,9 @@ static int batch_create(Batch& B) {
       double* d = mem.get<double>(cells);
       L.delta = d;
       L.lsum = mem.get<double>(4);
+      L.part = nullptr;
+      if (batch_blk_tile(c.ns[l]).ti != 0 && !(L.part = mem.get<double>(3 * kBatchBlkMax)))
+        return fail(MR_ENOMEM, "batched: level buffers");
       if (!L.e[0] || !L.e[1] || !L.rhs || !L.base || !L.sb || !d || !L.lsum) return fail(MR_ENOMEM, "batched: level buffers");
     }
   }
@@ -1026,12 +1229,15 @@ static int batch_solve(Batch& B, const double* const* delta, double* const* thet
     const size_t cells = (size_t)c.n * c.n * c.n;
     BBox& x = hb[b];
     double* r = rbuf + 8 * (size_t)b;
-    e = launch_residual(x.theta, x.lv[0].delta, c.n, 1.0, ShiftRef{nullptr, 0.0, 0.0}, nullptr,
+    // with the box's last <Sigma> taken out: sum b^2 - (sum b)^2 / N would otherwise cancel down to about
+    // 1e-10 of the reference norm, the size of a tight tolerance
+    e = launch_residual(x.theta, x.lv[0].delta, c.n, 1.0, ShiftRef{x.res, 1.0 / (double)cells, 0.0}, nullptr,
                         Reduce{scratch + 64, scounter, r}, s);
     if (e == hipSuccess) e = launch_sum(x.theta, cells, Reduce{scratch + 64, scounter, r + 2}, s);
     if (e == hipSuccess) e = launch_from_split(x.theta, theta[b], c.n, r + 2, 1.0 / (double)cells, s);
   }
   if (e == hipSuccess) e = hipMemcpyAsync(rh.data(), rbuf, rh.size() * sizeof(double), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(resinit.data(), resall, resinit.size() * sizeof(double), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "batched output");
   int status = MR_OK;
@@ -1051,7 +1257,7 @@ static int batch_solve(Batch& B, const double* const* delta, double* const* thet
       inf.cycles = hs[b].iters;
       inf.rel_residual = relf;
       inf.r0_norm = hs[b].r0;
-      inf.m_shift = -s0 / N3;
+      inf.m_shift = (resinit[8 * (size_t)b] + resinit[8 * (size_t)b + 1] - s0) / N3;
       const int nh = std::min(hs[b].iters + 1, 128);
       for (int k = 0; k < nh; ++k) inf.history[k] = hs[b].hist[k];
       inf.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();

@@ -52,7 +52,7 @@ struct Box {
   }
 };
 
-// u / D for 0 <= u < 2^13, 2 <= D < 32 (24-bit multiply; exact while u * D < 2^20).
+// u / D where u * D < 2^20 (24-bit multiply).
 template <int D>
 __device__ __forceinline__ int div_small(int u) {
   if ((D & (D - 1)) == 0) return u / D;
@@ -60,10 +60,38 @@ __device__ __forceinline__ int div_small(int u) {
   return (int)(__umul24((unsigned)u, M) >> 20);
 }
 
-// The cells of one local colour in the tile grown by S cells on every side, dealt to NT threads.
+// Loads of a whole field (at most 4 GiB) by 32-bit byte offset from scalar registers.
+template <typename T>
+struct Field {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ Field(const T* p, int n) : r(plane_rsrc(p, (unsigned)n * n * n * (unsigned)sizeof(T))) {}
+  __device__ __forceinline__ T operator[](unsigned byte_off) const {
+    if constexpr (sizeof(T) == 8)
+      return ld_rs(r, byte_off);
+    else
+      return ld_rs_f(r, byte_off);
+  }
+};
+
+// The planes a thread visits in a box: first, first + G, ...; byte offset of the plane in the mesh.
+template <int G>
+struct PlaneWalk {
+  unsigned gi, n, bytes;
+  __device__ __forceinline__ PlaneWalk(int first, int n_, unsigned plane_bytes)
+      : gi((unsigned)wrapi(first, n_)), n((unsigned)n_), bytes(plane_bytes) {}
+  __device__ __forceinline__ unsigned off() const { return __umul24(gi, bytes); }
+  __device__ __forceinline__ void next() {
+    const unsigned a = gi + G;
+    gi = min(a, a - n);   // one period back where that is not negative
+  }
+};
+
+// The cells of one local colour in the tile grown by S cells on every side, dealt to NT threads: a thread
+// keeps one position (j, m) and takes every G-th plane, so that rows, columns and their periodic images are
+// worked out once per stage and a further cell costs some ten instructions (with a division and a 64-bit
+// address for every cell, setting up was half of a launch's instructions).
 // loc[t] of a thread's cell: position in its colour's half of the box, bit 16 its parity in z, bit 17
-// set inside the tile; -1 past the end. Worked out once per launch: formed again at every use the
-// divisions were a third of the half-sweeps' instructions.
+// set inside the tile; -1 where there is none.
 constexpr int kLocQ = 1 << 16, kLocOwn = 1 << 17, kLocPos = kLocQ - 1;
 template <typename T>
 struct Same {
@@ -72,51 +100,81 @@ struct Same {
 template <class B, int TI, int TJ, int TK, int OFF, int S, int NT>
 struct Stage {
   static constexpr int EI = TI + 2 * S, EJ = TJ + 2 * S, EKH = (TK + 2 * S) / 2;
-  static constexpr int CELLS = EI * EJ * EKH;
-  static constexpr int N = (CELLS + NT - 1) / NT;   // cells per thread
+  static constexpr int POS = EJ * EKH, G = NT / POS;
+  static constexpr int N = (EI + G - 1) / G;   // cells per thread
   static constexpr int LO = OFF - S;
-  static_assert(N * NT < 8192 && B::HALF < kLocQ, "packed positions");
+  static_assert(G >= 1 && NT <= 1024 && POS < 1024 && B::HALF < kLocQ, "a position per thread, packed positions");
   int loc[N];
   // positions, and add + src of the mesh at them (and src2, when TWO)
   template <bool TWO, typename T>
   __device__ __forceinline__ void init(const B& b, int c, T add, const T* __restrict__ src,
                                        const typename Same<T>::type* __restrict__ src2, T (&v)[N], T (&v2)[N]) {
+    const int g = div_small<POS>((int)threadIdx.x), p = (int)threadIdx.x - g * POS;
+    const int rj = div_small<EKH>(p), mm = p - rj * EKH;
+    const int j = LO + rj, i0 = LO + g;
+    const bool own_j = (unsigned)(j - OFF) < (unsigned)TJ;
+    const unsigned plane = (unsigned)b.n * (unsigned)b.nh;
+    const unsigned row = (unsigned)(c ^ B::RED) * (plane * (unsigned)b.n) + __umul24((unsigned)wrapi(b.j0 + j, b.n), (unsigned)b.nh);
+    // the row's cell with the parity of the first plane (0) and with the other one (1): first of that
+    // parity at or after LO, 2 mm further
+    const int q0 = (i0 + j + c) & 1;
+    int pos[2];
+    unsigned col[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int q = q0 ^ x;
+      const int k = LO + ((LO + q) & 1) + 2 * mm;
+      const bool own = own_j && (unsigned)(k - OFF) < (unsigned)TK;
+      pos[x] = ((i0 * B::RJ + j) * B::RKH + (k >> 1)) | (q << 16) | (own ? kLocOwn : 0);
+      col[x] = (row + ((unsigned)wrapi(b.k0 + k, b.n) >> 1)) * (unsigned)sizeof(T);
+    }
+    const Field<T> f(src, b.n), f2(TWO ? src2 : src, b.n);
+    PlaneWalk<G> w(b.i0 + i0, b.n, plane * (unsigned)sizeof(T));
 #pragma unroll
     for (int t = 0; t < N; ++t) {
-      const int u = (int)threadIdx.x + t * NT;
-      const int r = div_small<EKH>(u), ri = div_small<EJ>(r);
-      const int i = LO + ri, j = LO + r - ri * EJ;
-      const int q = (i + j + c) & 1;                            // parity of the row's cells of this colour
-      const int k = LO + ((LO + q) & 1) + 2 * (u - r * EKH);    // first cell of that parity at or after LO
-      const bool in = CELLS % NT == 0 || u < CELLS;
-      const bool own = (unsigned)(i - OFF) < (unsigned)TI && (unsigned)(j - OFF) < (unsigned)TJ &&
-                       (unsigned)(k - OFF) < (unsigned)TK;
-      loc[t] = in ? ((i * B::RJ + j) * B::RKH + (k >> 1)) | (q ? kLocQ : 0) | (own ? kLocOwn : 0) : -1;
-      v[t] = add;
-      v2[t] = T(0);
-      if (in) {
-        const unsigned g = b.mesh(c, i, j, k);
-        v[t] = add + src[g];
-        if (TWO) v2[t] = src2[g];
-      }
+      const int x = (t * G) & 1;
+      const int i = i0 + t * G;
+      int e = pos[x] + t * G * B::RJ * B::RKH;
+      if (S > 0 && (unsigned)(i - OFF) >= (unsigned)TI) e &= ~kLocOwn;
+      const bool in = g < G && ((t + 1) * G <= EI || i < LO + EI);
+      loc[t] = in ? e : -1;
+      const unsigned o = w.off() + col[x];
+      v[t] = add + f[o];
+      v2[t] = TWO ? f2[o] : T(0);
+      w.next();
     }
   }
 };
 
-// Calls f(e, c, i, j, m, q) for every cell of the box this thread loads: position e in the box, local
-// colour c, row (i, j), column m, parity q in z (k = 2 m + q).
-template <class B, int NT, class F>
-__device__ __forceinline__ void for_box(F f) {
-  constexpr int NL = (2 * B::HALF + NT - 1) / NT;
+// Calls f(e, o, i, j, m, q) for every cell of the box this thread loads: position e in the box, byte offset o
+// in a mesh of T, row (i, j), column m, parity q in z (k = 2 m + q). Dealt as a stage's cells.
+template <typename T, class B, int NT, class F>
+__device__ __forceinline__ void for_box(const B& b, F f) {
+  constexpr int POS = B::RJ * B::RKH, G = NT / POS, N = (B::RI + G - 1) / G;
+  static_assert(G >= 1 && NT <= 1024, "a position per thread");
+  const int g = div_small<POS>((int)threadIdx.x), p = (int)threadIdx.x - g * POS;
+  const int j = div_small<B::RKH>(p), m = p - j * B::RKH;
+  if (g >= G) return;
+  const unsigned plane = (unsigned)b.n * (unsigned)b.nh, half = plane * (unsigned)b.n;
+  const unsigned row = __umul24((unsigned)wrapi(b.j0 + j, b.n), (unsigned)b.nh);
+  const int q0 = (g + j) & 1;   // of local colour 0 in the first plane
+  unsigned col[2];              // columns at parity q0 and at the other one
 #pragma unroll
-  for (int t = 0; t < NL; ++t) {
-    const int e = (int)threadIdx.x + t * NT;
-    if (e < 2 * B::HALF) {
-      const int c = e >= B::HALF ? 1 : 0, r = e - c * B::HALF;
-      const int ij = div_small<B::RKH>(r), m = r - ij * B::RKH;
-      const int i = div_small<B::RJ>(ij), j = ij - i * B::RJ;
-      f(e, c, i, j, m, (i + j + c) & 1);
+  for (int x = 0; x < 2; ++x)
+    col[x] = (row + ((unsigned)wrapi(b.k0 + 2 * m + (q0 ^ x), b.n) >> 1)) * (unsigned)sizeof(T);
+  PlaneWalk<G> w(b.i0 + g, b.n, plane * (unsigned)sizeof(T));
+  const int e0 = (g * B::RJ + j) * B::RKH + m;
+#pragma unroll
+  for (int t = 0; t < N; ++t) {
+    const int i = g + t * G;
+    if ((t + 1) * G > B::RI && i >= B::RI) break;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int x = (t * G + c) & 1;
+      f(c * B::HALF + e0 + t * G * B::RJ * B::RKH, w.off() + col[x] + (unsigned)(c ^ B::RED) * half * (unsigned)sizeof(T), i,
+        j, m, q0 ^ x);
     }
+    w.next();
   }
 }
 

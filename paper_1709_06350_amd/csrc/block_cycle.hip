@@ -74,7 +74,8 @@ __global__ void __launch_bounds__(NT) blk_down_kernel(BlkDownArgs a) {
 
   // every global load of the launch is issued here: theta of the box, delta of each stage's cells,
   // the partial sums of the shift
-  for_box<B, NT>([&](int e, int c, int i, int j, int m, int q) { th[e] = a.theta[b.mesh(c, i, j, 2 * m + q)]; });
+  const Field<double> theta(a.theta, a.n);
+  for_box<double, B, NT>(b, [&](int e, unsigned o, int i, int j, int m, int q) { th[e] = theta[o]; });
   double d4[s4.N], d3[s3.N], d2[s2.N], d1[s1.N], r4[s4.N], r3[s3.N], r2[s2.N], r1[s1.N];
   s4.template init<TAU>(b, R, 1.0, a.delta, a.rd, d4, r4);
   s3.template init<TAU>(b, K, 1.0, a.delta, a.rd, d3, r3);
@@ -195,13 +196,14 @@ __global__ void __launch_bounds__(NT) blk_up_kernel(BlkUpArgs a) {
   s1.template init<HAS_F>(b, R, 1.0, a.delta, a.f, d1, f1);
   s0.template init<HAS_F>(b, K, 1.0, a.delta, a.f, d0, f0);
   const double C = block_total<NT>(a.c_part, a.c_count, red) * a.c_scale;   // ends in a barrier: ec is complete
-  for_box<B, NT>([&](int e, int c, int i, int j, int m, int q) {
+  const Field<double> theta(a.theta, a.n);
+  for_box<double, B, NT>(b, [&](int e, unsigned o, int i, int j, int m, int q) {
     // parent's position in ec and the neighbour towards the fine cell
     const double* __restrict__ p = ec + ((i >> 1) + 1) * (QJ * QK) + ((j >> 1) + 1) * QK + m + 1;
     const int ni = (i & 1) ? QJ * QK : -QJ * QK, nj = (j & 1) ? QK : -QK, nk = q ? 1 : -1;
-    auto row = [&](int o) { return 0.75 * p[o] + 0.25 * p[o + nk]; };
+    auto row = [&](int s) { return 0.75 * p[s] + 0.25 * p[s + nk]; };
     const double corr = 0.75 * (0.75 * row(0) + 0.25 * row(nj)) + 0.25 * (0.75 * row(ni) + 0.25 * row(ni + nj));
-    th[e] = a.theta[b.mesh(c, i, j, 2 * m + q)] + corr;
+    th[e] = theta[o] + corr;
   });
   __syncthreads();
   const double h2 = a.h2, ih2 = a.ih2;
@@ -446,7 +448,7 @@ __global__ void __launch_bounds__(NT) blk_tail_kernel(BlkTailArgs a) {
           const int q = (i + j + c) & 1;
           const double* __restrict__ x = ec + (((i >> 1) + 1) * (NB + 2) + (j >> 1) + 1) * (NB + 2) + m + 1;
           const int ni = ((i & 1) ? 1 : -1) * (NB + 2) * (NB + 2), nj = ((j & 1) ? 1 : -1) * (NB + 2), nk = q ? 1 : -1;
-          auto row = [&](int o) { return 0.75 * x[o] + 0.25 * x[o + nk]; };
+          auto row = [&](int s) { return 0.75 * x[s] + 0.25 * x[s + nk]; };
           A.put(c, p, A.get(c, p) + 0.75 * (0.75 * row(0) + 0.25 * row(nj)) + 0.25 * (0.75 * row(ni) + 0.25 * row(ni + nj)));
         }
     __syncthreads();

@@ -117,11 +117,10 @@ __device__ void lin_down_body(const LinDownArgs& a, int logical, int blk, LinBox
   B b;
   b.init(logical, a.n);
   const int tid = threadIdx.x;
-  const float* __restrict__ basef = reinterpret_cast<const float*>(a.base);
-  for_box<B, NT>([&](int x, int c, int i, int j, int m, int q) {
-    const unsigned g = b.mesh(c, i, j, 2 * m + q);
-    sh.bs[x] = basef[g];
-    if (!ZERO) sh.e[x] = a.e[g];
+  const Field<float> basef(reinterpret_cast<const float*>(a.base), a.n), e_in(a.e, a.n);
+  for_box<float, B, NT>(b, [&](int x, unsigned o, int i, int j, int m, int q) {
+    sh.bs[x] = basef[o];
+    if (!ZERO) sh.e[x] = e_in[o];
   });
   float b4[s4.N], b3[s3.N], b2[s2.N], b1[s1.N], r4[s4.N], r3[s3.N], r2[s2.N], r1[s1.N];
   s4.template init<true>(b, R, 0.0f, a.sb, a.rhs, b4, r4);
@@ -219,15 +218,14 @@ __device__ void lin_up_body(const LinUpArgs& a, int logical, int blk, LinBoxLds<
   const float bscl = (float)a.bq[0], h2 = a.h2, ih2 = a.ih2;
   const float C = (float)(block_total<NT>(a.c.part, a.c.count, reinterpret_cast<double(*)[1]>(sh.red)) *
                           a.c.scale);   // ends in a barrier: ec is complete
-  const float* __restrict__ basef = reinterpret_cast<const float*>(a.base);
-  for_box<B, NT>([&](int x, int c, int i, int j, int m, int q) {
+  const Field<float> basef(reinterpret_cast<const float*>(a.base), a.n), e_in(a.e, a.n);
+  for_box<float, B, NT>(b, [&](int x, unsigned o, int i, int j, int m, int q) {
     const float* __restrict__ p = sh.ec + ((i >> 1) + 1) * (QJ * QK) + ((j >> 1) + 1) * QK + m + 1;
     const int ni = (i & 1) ? QJ * QK : -QJ * QK, nj = (j & 1) ? QK : -QK, nk = q ? 1 : -1;
-    auto row = [&](int o) { return 0.75f * p[o] + 0.25f * p[o + nk]; };
+    auto row = [&](int s) { return 0.75f * p[s] + 0.25f * p[s + nk]; };
     const float corr = 0.75f * (0.75f * row(0) + 0.25f * row(nj)) + 0.25f * (0.75f * row(ni) + 0.25f * row(ni + nj));
-    const unsigned g = b.mesh(c, i, j, 2 * m + q);
-    sh.e[x] = a.e[g] + corr;
-    sh.bs[x] = basef[g];
+    sh.e[x] = e_in[o] + corr;
+    sh.bs[x] = basef[o];
   });
   __syncthreads();
   double acc = 0.0;
@@ -500,7 +498,7 @@ __device__ void lin_tail2_body(const LinTail2Args& a, LinTail2Lds<NA, NB>& sh) {
           const int q = (i + j + c) & 1;
           const float* __restrict__ x = sh.ec + (((i >> 1) + 1) * (NB + 2) + (j >> 1) + 1) * (NB + 2) + m + 1;
           const int ni = ((i & 1) ? 1 : -1) * (NB + 2) * (NB + 2), nj = ((j & 1) ? 1 : -1) * (NB + 2), nk = q ? 1 : -1;
-          auto row = [&](int o) { return 0.75f * x[o] + 0.25f * x[o + nk]; };
+          auto row = [&](int s) { return 0.75f * x[s] + 0.25f * x[s + nk]; };
           A.put(sh.eA, c, p,
                 A.get(c, p) + 0.75f * (0.75f * row(0) + 0.25f * row(nj)) + 0.25f * (0.75f * row(ni) + 0.25f * row(ni + nj)));
         }

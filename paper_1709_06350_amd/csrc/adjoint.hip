@@ -480,7 +480,7 @@ static int row_threads_a(int n) { return n < 64 ? 64 : (n < 256 ? n : 256); }
 
 // ---- half-sweep launch and tile choice ----------------------------------------------------
 
-#define MR_AP_TILES(X) X(64, 4) X(64, 8) X(32, 8) X(16, 16) X(8, 16) X(8, 8) X(4, 8)
+#define MR_AP_TILES(X) X(48, 8) X(40, 8) X(64, 4) X(64, 8) X(32, 8) X(16, 16) X(8, 16) X(8, 8) X(4, 8)
 
 struct AdjCfg {
   int tm = 0, tj = 0, ci = 0;   // tm == 0: the row kernel
@@ -605,7 +605,7 @@ static int tune_adj_sweep(const AdjSweepArgs& base, hipStream_t s, AdjCfg* out) 
   bool recorded = false;
   {
     std::vector<int> rec;
-    if (tuning_lookup("adj64.v1", dev, n, rec))
+    if (tuning_lookup(tile_kind("adj64.v1", "adj64.v2", n), dev, n, rec))
       for (size_t i = 0; i < cand.size() && !recorded; ++i)
         if (code(cand[i]) == rec) {
           bi = i;
@@ -619,7 +619,7 @@ static int tune_adj_sweep(const AdjSweepArgs& base, hipStream_t s, AdjCfg* out) 
     std::lock_guard<std::mutex> lk(g_adj_tune_mu);
     g_adj_tuned[{dev, n}] = best_c;
   }
-  if (!recorded) tuning_record("adj64.v1", dev, n, code(best_c));
+  if (!recorded) tuning_record(tile_kind("adj64.v1", "adj64.v2", n), dev, n, code(best_c));
   *out = best_c;
   return MR_OK;
 }

@@ -491,8 +491,8 @@ __global__ void __launch_bounds__(256) b_aa_combine_kernel(const BBox* boxes, co
 
 // ---- FP32 sweep tile tuner ----------------------------------------------------------------
 
-#define MR_BLIN_TILES(X) X(64, 16) X(64, 8) X(64, 4) X(32, 8) X(16, 16) X(8, 16) X(4, 8) X(2, 4)
-#define MR_BRT_TILES(X) X(64, 8) X(32, 8) X(16, 8) X(8, 8) X(4, 8)
+#define MR_BLIN_TILES(X) X(48, 16) X(48, 8) X(40, 16) X(40, 8) X(64, 16) X(64, 8) X(64, 4) X(32, 8) X(16, 16) X(8, 16) X(4, 8) X(2, 4)
+#define MR_BRT_TILES(X) X(48, 8) X(40, 8) X(64, 8) X(32, 8) X(16, 8) X(8, 8) X(4, 8)
 
 static hipError_t launch_b_lin_sweep(const BBox* boxes, const int* cls, int nb, const TileCfg& t, int l, int colour, int cur,
                                      int n, double h, hipStream_t s, bool zero_black = false) {
@@ -522,7 +522,7 @@ static hipError_t launch_b_lin_sweep(const BBox* boxes, const int* cls, int nb, 
 static std::vector<TileCfg> lin_candidates(int n) {
   std::vector<TileCfg> out;
   const int nh = n / 2;
-  static const int shapes[][2] = {{64, 16}, {64, 8}, {64, 4}, {32, 8}, {16, 16}, {8, 16}, {4, 8}, {2, 4}};
+  static const int shapes[][2] = {{48, 16}, {48, 8}, {40, 16}, {40, 8}, {64, 16}, {64, 8}, {64, 4}, {32, 8}, {16, 16}, {8, 16}, {4, 8}, {2, 4}};
   auto fits = [&](const int* sh) { return nh % sh[0] == 0 && sh[0] <= nh && n % sh[1] == 0 && sh[1] <= n; };
   bool big = false;
   for (const auto& sh : shapes) big = big || (fits(sh) && sh[0] * sh[1] >= 128);
@@ -573,7 +573,7 @@ int tune_lin_tiles(int n, hipStream_t s, TileCfg* out, float* ms_out) {
   // a recorded choice that is still a candidate: the tile and the time of one sweep (float bits)
   {
     std::vector<int> rec;
-    if (tuning_lookup("blin32.v1", dev, n, rec) && rec.size() == 8)
+    if (tuning_lookup(tile_kind("blin32.v1", "blin32.v2", n), dev, n, rec) && rec.size() == 8)
       for (const TileCfg& t : lin_candidates(n)) {
         std::vector<int> code = tile_code(t);
         if (!std::equal(code.begin(), code.end(), rec.begin())) continue;
@@ -676,7 +676,7 @@ int tune_lin_tiles(int n, hipStream_t s, TileCfg* out, float* ms_out) {
     int bits = 0;
     std::memcpy(&bits, &best_ms, sizeof bits);
     code.push_back(bits);
-    tuning_record("blin32.v1", dev, n, code);
+    tuning_record(tile_kind("blin32.v1", "blin32.v2", n), dev, n, code);
   }
   *out = cand[bi];
   if (ms_out) *ms_out = best_ms;
@@ -709,7 +709,7 @@ struct SizeClass {
 // units of 4 planes, chunks of at least 8 planes) that gives each box about 64 blocks. It depends on
 // n only, so a box is reduced in the same order whatever else is in the batch.
 BTile pick_btile(int n) {
-  static const int pref[][2] = {{64, 8}, {32, 8}, {16, 8}, {8, 8}, {4, 8}};
+  static const int pref[][2] = {{64, 8}, {48, 8}, {40, 8}, {32, 8}, {16, 8}, {8, 8}, {4, 8}};
   BTile t;
   if (n % 8 != 0) return t;
   for (const auto& p : pref) {

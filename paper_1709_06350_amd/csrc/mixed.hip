@@ -33,7 +33,7 @@
 namespace mr {
 
 // Compiled tile shapes (tm columns of m, tj rows) of the FP32 linear sweeps.
-#define MR_LIN_TILES(X) X(64, 8) X(64, 4) X(64, 16) X(32, 16) X(32, 8) X(16, 16) X(8, 16) X(4, 8) X(2, 4)
+#define MR_LIN_TILES(X) X(48, 16) X(48, 8) X(40, 16) X(40, 8) X(64, 8) X(64, 4) X(64, 16) X(32, 16) X(32, 8) X(16, 16) X(8, 16) X(4, 8) X(2, 4)
 
 template <int TM, int TJ>
 __global__ void __launch_bounds__(TM * TJ) lin_half_sweep_tiled(LinSweepArgs a) {
@@ -205,7 +205,7 @@ __global__ void __launch_bounds__(TM * TJ) mixed_resid64_tiled(ResidTiledArgs a)
   mixed_resid64_tiled_body<TM, TJ>(a, xcd_remap(blockIdx.x, gridDim.x), blockIdx.x, gridDim.x, lds);
 }
 
-#define MR_RR_TILES(X) X(64, 8) X(32, 8) X(16, 8) X(8, 8) X(4, 8)
+#define MR_RR_TILES(X) X(48, 8) X(40, 8) X(64, 8) X(32, 8) X(16, 8) X(8, 8) X(4, 8)
 
 static const void* rr_tiled_kernel(int tm, int tj) {
 #define MR_RR_PTR(TM, TJ) \
@@ -215,7 +215,7 @@ static const void* rr_tiled_kernel(int tm, int tj) {
   return nullptr;
 }
 
-#define MR_RT_TILES(X) X(64, 8) X(32, 8) X(16, 8) X(8, 8) X(4, 8)
+#define MR_RT_TILES(X) X(48, 8) X(40, 8) X(64, 8) X(32, 8) X(16, 8) X(8, 8) X(4, 8)
 
 static const void* resid_tiled_kernel(int tm, int tj) {
 #define MR_RT_PTR(TM, TJ) \
@@ -229,7 +229,7 @@ static const void* resid_tiled_kernel(int tm, int tj) {
 // threads = tm * tj / per) that divides the mesh, the plane axis split in units of 4 planes so
 // that the grid fills whole waves of the device's resident block slots as well as possible.
 // Returns false when no tile applies.
-static const int kPref8[][2] = {{64, 8}, {32, 8}, {16, 8}, {8, 8}, {4, 8}};
+static const int kPref8[][2] = {{64, 8}, {48, 8}, {40, 8}, {32, 8}, {16, 8}, {8, 8}, {4, 8}};
 
 template <typename Get, size_t NP>
 static bool tiled_cfg(int n, Get get, int per, int& tm, int& tj, int& nchunks, const int (&pref)[NP][2]) {
@@ -409,49 +409,58 @@ hipError_t launch_lin_fused(const LinFusedArgs& a, const LinFusedCfg& t, hipStre
   return hipErrorInvalidValue;
 }
 
+template <int TM, int TJ>
+static hipError_t launch_apply_tile(LinApplyArgs a, int k, hipStream_t s, bool* done) {
+  const int n = a.n;
+  if (*done || (n / 2) % TM != 0 || n % TJ != 0 || n % 4 != 0) return hipSuccess;
+  const int tiles = (n / TJ) * (n / 2 / TM);
+  // up to one block per CU: more blocks cost more in the per-block release of the reduction
+  // than they gain in occupancy (the blocks have 16 waves each)
+  int nch = 1;
+  while (tiles * nch * 2 <= kApplyBlocks && (n / (nch * 2)) % 4 == 0 && n % (nch * 2) == 0 && n / (nch * 2) >= 16) nch *= 2;
+  if (tiles * nch > kKryBlocks || (n / nch) % 4 != 0) return hipSuccess;
+  a.tiles_j = n / TJ;
+  a.tiles_m = n / 2 / TM;
+  a.ci = n / nch;
+  const unsigned blocks = (unsigned)(tiles * nch);
+  *done = true;
+  switch (k) {
+#define MR_AD_CASE(KK)                                                                                          \
+    case KK:                                                                                                    \
+      hipLaunchKernelGGL((lin_apply_dots<TM, TJ, KK>), dim3(blocks), dim3(2 * TM * TJ), 0, s, a);              \
+      break;
+    MR_AD_CASE(1) MR_AD_CASE(2) MR_AD_CASE(3) MR_AD_CASE(4) MR_AD_CASE(5) MR_AD_CASE(6) MR_AD_CASE(7)
+    MR_AD_CASE(8)
+#undef MR_AD_CASE
+  }
+  return hipGetLastError();
+}
+
 // w = J z on an n^3 mesh (both colours) and the sums w v_j (j < k), w, w^2 into result[0 .. k + 1]:
-// one pipelined launch with the projections fused where a 64 x 8 tile fits (at most kKryBlocks
+// one pipelined launch with the projections fused where a compiled tile fits (at most kKryBlocks
 // blocks), otherwise the row kernel followed by the dot-product kernel.
 hipError_t launch_lin_apply_dots(const float* z, const int* baseq, const double* bq, const float* sb, int n, double h,
                                  float* w, const KryPtrs& v, int k, double* partials, unsigned* counter, double* result,
                                  hipStream_t s) {
-  constexpr int TM = 64, TJ = 8;
   if (k < 1 || k > kKryMax) return hipErrorInvalidValue;
-  if ((n / 2) % TM == 0 && n % TJ == 0 && n % 4 == 0) {
-    const int tiles = (n / TJ) * (n / 2 / TM);
-    // up to one block per CU: more blocks cost more in the per-block release of the reduction
-    // than they gain in occupancy (the blocks have 16 waves each)
-    int nch = 1;
-    while (tiles * nch * 2 <= kApplyBlocks && (n / (nch * 2)) % 4 == 0 && n / (nch * 2) >= 16) nch *= 2;
-    if (tiles * nch <= kKryBlocks && (n / nch) % 4 == 0) {
-      LinApplyArgs a{};
-      a.z = z;
-      a.base = baseq;
-      a.bq = bq;
-      a.sb = sb;
-      a.w = w;
-      a.n = n;
-      a.ih2 = (float)(1.0 / (h * h));
-      a.tiles_j = n / TJ;
-      a.tiles_m = n / 2 / TM;
-      a.ci = n / nch;
-      a.v = v;
-      a.partials = partials;
-      a.counter = counter;
-      a.result = result;
-      const unsigned blocks = (unsigned)(tiles * nch);
-      switch (k) {
-#define MR_AD_CASE(KK)                                                                                          \
-        case KK:                                                                                                \
-          hipLaunchKernelGGL((lin_apply_dots<TM, TJ, KK>), dim3(blocks), dim3(2 * TM * TJ), 0, s, a);          \
-          break;
-        MR_AD_CASE(1) MR_AD_CASE(2) MR_AD_CASE(3) MR_AD_CASE(4) MR_AD_CASE(5) MR_AD_CASE(6) MR_AD_CASE(7)
-        MR_AD_CASE(8)
-#undef MR_AD_CASE
-      }
-      return hipGetLastError();
-    }
-  }
+  LinApplyArgs a{};
+  a.z = z;
+  a.base = baseq;
+  a.bq = bq;
+  a.sb = sb;
+  a.w = w;
+  a.n = n;
+  a.ih2 = (float)(1.0 / (h * h));
+  a.v = v;
+  a.partials = partials;
+  a.counter = counter;
+  a.result = result;
+  bool done = false;
+  hipError_t e = launch_apply_tile<64, 8>(a, k, s, &done);
+  if (e == hipSuccess) e = launch_apply_tile<48, 8>(a, k, s, &done);
+  if (e == hipSuccess) e = launch_apply_tile<40, 8>(a, k, s, &done);
+  if (e == hipSuccess) e = launch_apply_tile<32, 8>(a, k, s, &done);
+  if (e != hipSuccess || done) return e;
   hipLaunchKernelGGL(lin_apply_row_kernel, dim3(rows_blocks(n)), dim3(row_threads(n)), 0, s, z, baseq, bq, sb, n,
                      (float)(1.0 / (h * h)), w);
   const size_t cells = (size_t)n * n * n;
@@ -795,7 +804,7 @@ static int tune_lin_sweep(Ctx* c, int l, LinSched* out) {
   bool recorded = false;
   {
     std::vector<int> rec;
-    if (tuning_lookup("lin32.v1", dev, n, rec))
+    if (tuning_lookup(tile_kind("lin32.v1", "lin32.v2", n), dev, n, rec))
       for (size_t i = 0; i < ok.size() && !recorded; ++i)
         if (code(ok[i]) == rec) {
           bi = i;
@@ -811,7 +820,7 @@ static int tune_lin_sweep(Ctx* c, int l, LinSched* out) {
     std::lock_guard<std::mutex> lk(g_lin_tune_mu);
     g_lin_tuned[{dev, n}] = best_t;
   }
-  if (!ok.empty() && !recorded) tuning_record("lin32.v1", dev, n, code(best_t));
+  if (!ok.empty() && !recorded) tuning_record(tile_kind("lin32.v1", "lin32.v2", n), dev, n, code(best_t));
   *out = best_t;
   return MR_OK;
 }
@@ -853,7 +862,7 @@ static int tune_lin_rr(Ctx* c, int l, int* tm, int* tj, int* nch) {
   bool recorded = false;
   {
     std::vector<int> rec;
-    if (tuning_lookup("linrr32.v1", dev, n, rec))
+    if (tuning_lookup(tile_kind("linrr32.v1", "linrr32.v2", n), dev, n, rec))
       for (size_t i = 0; i < cand.size() && !recorded; ++i)
         if (cand[i] == rec) {
           bi = i;
@@ -875,7 +884,7 @@ static int tune_lin_rr(Ctx* c, int l, int* tm, int* tj, int* nch) {
     std::lock_guard<std::mutex> lk(g_rr_tune_mu);
     g_rr_tuned[{dev, n}] = cand[bi];
   }
-  if (!recorded) tuning_record("linrr32.v1", dev, n, cand[bi]);
+  if (!recorded) tuning_record(tile_kind("linrr32.v1", "linrr32.v2", n), dev, n, cand[bi]);
   *tm = cand[bi][0];
   *tj = cand[bi][1];
   *nch = cand[bi][2];

@@ -775,7 +775,7 @@ __global__ void __launch_bounds__(TM * TJ) tau_pipe(const double* __restrict__ t
 
 // Tile and chunk count of the pipelined FAS right-hand side (as for the defect + restriction).
 bool tau_pipe_cfg(int n, int& tm, int& tj, int& nchunks) {
-  static const int pref[][2] = {{64, 8}, {32, 8}, {16, 8}, {8, 8}, {4, 8}};
+  static const int pref[][2] = {{64, 8}, {48, 8}, {40, 8}, {32, 8}, {16, 8}, {8, 8}, {4, 8}};
   if (n % 8 != 0) return false;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -786,7 +786,7 @@ bool tau_pipe_cfg(int n, int& tm, int& tj, int& nchunks) {
     const void* k = nullptr;
 #define MR_TP_PTR(TM, TJ) \
     if (p[0] == TM && p[1] == TJ) k = reinterpret_cast<const void*>(&tau_pipe<TM, TJ>);
-    MR_TP_PTR(64, 8) MR_TP_PTR(32, 8) MR_TP_PTR(16, 8) MR_TP_PTR(8, 8) MR_TP_PTR(4, 8)
+    MR_TP_PTR(64, 8) MR_TP_PTR(48, 8) MR_TP_PTR(40, 8) MR_TP_PTR(32, 8) MR_TP_PTR(16, 8) MR_TP_PTR(8, 8) MR_TP_PTR(4, 8)
 #undef MR_TP_PTR
     int bpc = 0;
     if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, k, p[0] * p[1], 0) != hipSuccess || bpc < 1) continue;
@@ -818,7 +818,7 @@ hipError_t launch_tau_pipe(const double* th, const double* delta, const double* 
     *done = true;                                                                                              \
     return hipGetLastError();                                                                                  \
   }
-  MR_TP_LAUNCH(64, 8) MR_TP_LAUNCH(32, 8) MR_TP_LAUNCH(16, 8) MR_TP_LAUNCH(8, 8) MR_TP_LAUNCH(4, 8)
+  MR_TP_LAUNCH(64, 8) MR_TP_LAUNCH(48, 8) MR_TP_LAUNCH(40, 8) MR_TP_LAUNCH(32, 8) MR_TP_LAUNCH(16, 8) MR_TP_LAUNCH(8, 8) MR_TP_LAUNCH(4, 8)
 #undef MR_TP_LAUNCH
   return hipSuccess;
 }
@@ -1221,7 +1221,9 @@ static bool tile_ok(const TileCfg& t, int n, int threads) {
   X(64, 8, 2) X(64, 4, 1) X(64, 8, 1) X(64, 16, 4) X(32, 8, 1) X(32, 16, 2) X(16, 16, 1) \
   X(16, 32, 2) X(8, 16, 1) X(8, 8, 1) X(4, 8, 1) X(4, 16, 2) X(2, 4, 1) X(2, 8, 1)
 
-#define MR_HP_TILES(X) X(64, 8) X(64, 4) X(64, 16) X(32, 8) X(32, 16) X(16, 16)
+// 48 and 40 columns: meshes of 96 2^k and 80 2^k cells a side, whose widest power-of-two tile has 16 columns or
+// fewer at 96 and 160 (a third of the loads are then halo).
+#define MR_HP_TILES(X) X(64, 8) X(64, 4) X(64, 16) X(32, 8) X(32, 16) X(16, 16) X(48, 16) X(48, 8) X(40, 16) X(40, 8)
 
 bool half_sweep_tile_supported(int tm, int tj, int cpt) {
 #define MR_HS_MATCH(TM, TJ, CPT) if (tm == TM && tj == TJ && cpt == CPT) return true;
@@ -1277,7 +1279,7 @@ bool half_sweep_pipe_supported(int tm, int tj) {
   return false;
 }
 
-#define MR_DR_TILES(X) X(64, 8) X(64, 4) X(32, 8) X(32, 4) X(16, 8) X(8, 8) X(4, 8)
+#define MR_DR_TILES(X) X(48, 8) X(40, 8) X(64, 8) X(64, 4) X(32, 8) X(32, 4) X(16, 8) X(8, 8) X(4, 8)
 
 // Tile and chunk count of the pipelined defect + restriction (chunks are multiples of 4 planes).
 struct DefectCfg {
@@ -1386,7 +1388,7 @@ int tune_defect(const DefectArgs& a, hipStream_t s) {
   MR_DR_TILES(MR_DR_ADD)
 #undef MR_DR_ADD
   if (cand.empty()) return MR_OK;
-  const char* kind = has_f ? "defect64f.v1" : "defect64.v1";
+  const char* kind = has_f ? tile_kind("defect64f.v1", "defect64f.v2", n) : tile_kind("defect64.v1", "defect64.v2", n);
   {
     std::vector<int> rec;
     if (tuning_lookup(kind, dev, n, rec))
@@ -1629,7 +1631,7 @@ int tune_sweep(int n, double* th_a, double* th_b, double* delta, double* partial
   };
   {
     std::vector<int> rec;
-    if (tuning_lookup("sweep64.v1", dev, n, rec))
+    if (tuning_lookup(tile_kind("sweep64.v1", "sweep64.v2", n), dev, n, rec))
       for (const SweepCand& c : all)
         if (code(c) == rec) {
           *use_fused = c.fused;
@@ -1692,7 +1694,7 @@ int tune_sweep(int n, double* th_a, double* th_b, double* delta, double* partial
     g_sweep_tuned[{dev, n}] = {best_fused, best_cfg};
     g_half_tuned[{dev, n}] = best_two;
   }
-  if (!all.empty()) tuning_record("sweep64.v1", dev, n, code(all[bk]));
+  if (!all.empty()) tuning_record(tile_kind("sweep64.v1", "sweep64.v2", n), dev, n, code(all[bk]));
   *use_fused = best_fused;
   *cfg = best_cfg;
   *two = best_two;

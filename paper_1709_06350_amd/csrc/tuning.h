@@ -22,6 +22,12 @@ inline std::vector<int> tile_code(const TileCfg& t) {
   return {t.tm, t.tj, t.ci, t.tiles_j, t.tiles_m, t.cpt, t.pipe ? 1 : 0};
 }
 
+// The name of a tuner's records for a mesh of n^3 cells: those of meshes that the 48- or 40-column tiles divide
+// are apart from the ones made before these tiles were among the candidates.
+inline const char* tile_kind(const char* plain, const char* wide, int n) {
+  return (n / 2) % 48 == 0 || (n / 2) % 40 == 0 ? wide : plain;
+}
+
 // The recorded choice of tuner `kind` for mesh size n on device dev, if there is one.
 bool tuning_lookup(const char* kind, int dev, int n, std::vector<int>& vals);
 // Records (and writes to the file, when one is in use) the choice of tuner `kind`.

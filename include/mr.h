@@ -146,7 +146,7 @@ int mr_levels(const mr_ctx* ctx);
  * colours), sched[1] = tile width in columns m (cells of one colour along k), sched[2] = tile
  * height in rows j, sched[3] = number of chunks the planes i are split into. mr_create picks each
  * level's schedule by timing the candidates on this device; all schedules compute the same update
- * and differ only in the rounding order of the sums of Sigma. Levels of 64 cells and fewer a side run
+ * and differ only in the rounding order of the sums of Sigma. Levels of 80 cells and fewer a side run
  * the default cycle (two sweeps before and after) in a block form of several sweeps a launch instead;
  * a level pinned with mr_set_schedule, every level above it, and the finest level while
  * mr_timing_enable is on run sweeps on their schedules. For callers that need the schedule

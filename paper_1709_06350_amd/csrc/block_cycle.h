@@ -5,8 +5,8 @@
 
 namespace mr {
 
-constexpr int kBlkMaxN = 64;        // largest level of the block form
-constexpr int kBlkMaxBlocks = 256;  // blocks (partial sums) of a launch
+constexpr int kBlkMaxN = 80;        // largest level of the block form
+constexpr int kBlkMaxBlocks = 512;  // blocks (partial sums) of a launch
 
 // Shift of a launch: C = c_scale * (sum of c_part[0 .. c_count)).
 struct BlkDownArgs {

@@ -466,12 +466,18 @@ __global__ void __launch_bounds__(NT) blk_tail_kernel(BlkTailArgs a) {
 // Tile of a level: the smallest compiled one whose blocks are no more than the 256 compute units (a
 // block's time goes with its cells and their halo, so a smaller tile is faster while units are idle;
 // past that its larger halo costs more than it saves): 4^3 to 24^3, 4 x 4 x 8 at 32^3, 4 x 8 x 8 at
-// 40^3, 8^3 at 48^3, 8 x 8 x 16 at 64^3.
+// 40^3, 8^3 at 48^3, 8 x 8 x 16 at 64^3. At 80^3 the largest runs twice as many: a solve takes 3.5 ms, with
+// the plain launches there 4.7. 96^3 (864 blocks) stays with those: 4.4 ms either way, the adjoint 9.2 and 7.7.
 BlkTile blk_tile(int n) {
   static const BlkTile tiles[] = {{4, 4, 4}, {4, 4, 8}, {4, 8, 8}, {8, 8, 8}, {8, 8, 16}};
-  for (const BlkTile& t : tiles)
-    if (n % t.ti == 0 && n % t.tj == 0 && n % t.tk == 0 && (n / t.ti) * (n / t.tj) * (n / t.tk) <= 256) return t;
-  return BlkTile{0, 0, 0};
+  BlkTile best{0, 0, 0};
+  for (const BlkTile& t : tiles) {
+    if (n % t.ti != 0 || n % t.tj != 0 || n % t.tk != 0) continue;
+    const int blocks = (n / t.ti) * (n / t.tj) * (n / t.tk);
+    if (blocks <= kBlkMaxBlocks) best = t;
+    if (blocks <= 256) break;
+  }
+  return best;
 }
 
 bool blk_level_supported(int n) { return n >= 16 && n <= kBlkMaxN && blk_tile(n).ti != 0; }

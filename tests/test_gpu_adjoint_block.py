@@ -1,6 +1,6 @@
-"""The block form of the adjoint cycle on meshes of 64^3 cells and below (adj_block.hip).
+"""The block form of the adjoint cycle on meshes of 80^3 cells and below (adj_block.hip).
 
-Every compiled tile as the finest level (20, 24: 4^3; 32; 40; 48; 64) and below the plain half-sweeps (96,
+Every compiled tile as the finest level (20, 24: 4^3; 32; 40; 48; 64, 80) and below the plain half-sweeps (96,
 160), with the three tails (8^3 over 4^3, 12^3 over 6^3, 10^3), against the same solve with the row
 kernels on every level (MR_FLAG_ADJ_ROWS). Tolerance: each gradient solves its system to a relative
 residual of 1e-10, which leaves an error of at most that times the ratio of the mean square wavenumber
@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 from paper_1709_06350_amd import mr  # noqa: E402
 
 
-@pytest.mark.parametrize("n,depth", [(20, 0), (24, 0), (32, 2), (40, 0), (48, 0), (64, 0), (96, 0), (160, 0)])
+@pytest.mark.parametrize("n,depth", [(20, 0), (24, 0), (32, 2), (40, 0), (48, 0), (64, 0), (80, 0), (96, 0), (160, 0)])
 def test_block_form_matches_row_kernels(n, depth):
     require_gpu()
     announce(f"adjoint block cycle n={n} depth={depth}")

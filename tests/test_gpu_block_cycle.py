@@ -1,7 +1,7 @@
-"""The block form of the FAS cycle on meshes of 64^3 cells and below (block_cycle.hip).
+"""The block form of the FAS cycle on meshes of 80^3 cells and below (block_cycle.hip).
 
 Sizes: every compiled tile as the finest level (16 and 24: 4^3; 20: 4^3 over a coarsest 10^3; 32:
-4 x 4 x 8; 40: 4 x 8 x 8; 48: 8^3; 64: 8 x 8 x 16) and as a level below the plain sweeps (96, 128, 160).
+4 x 4 x 8; 40: 4 x 8 x 8; 48: 8^3; 64 and 80: 8 x 8 x 16) and as a level below the plain sweeps (96, 128, 160).
 The reference is the oracle's solution where it is quick, and the library's plain launches
 (MR_FLAG_TWO_PASS switches the block form off) elsewhere.
 
@@ -38,7 +38,7 @@ def test_small_meshes_match_oracle(n):
     assert np.linalg.norm(theta - ref) <= 1e-9 * np.linalg.norm(ref)
 
 
-@pytest.mark.parametrize("n", [16, 32, 40, 48, 64, 96, 128, 160])
+@pytest.mark.parametrize("n", [16, 32, 40, 48, 64, 80, 96, 128, 160])
 def test_block_form_reaches_the_plain_cycles_solution(n):
     require_gpu()
     announce(f"block cycle vs plain launches n={n}")

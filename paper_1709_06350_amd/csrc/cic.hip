@@ -34,12 +34,42 @@ __device__ __forceinline__ void wrap_coord(double x, int n, int& i0, int& i1, do
   i1 = i0 + 1 == n ? 0 : i0 + 1;
 }
 
+// The same for the three coordinates of a particle; false if one is not finite. A coordinate of [0, n) is
+// its own wrapped value (x / n rounds below 1 there, so the floor is 0) and its own integer part rounded to
+// zero: a particle inside the box, as nearly all are, needs no division, floor or finiteness test, which
+// were half of the instructions of the counting and sorting passes.
+__device__ __forceinline__ bool wrap_particle(double x, double y, double z, int n, int (&i0)[3], int (&i1)[3],
+                                              double (&f)[3]) {
+  const double dn = (double)n;
+  if ((x >= 0.0) & (x < dn) & (y >= 0.0) & (y < dn) & (z >= 0.0) & (z < dn)) {
+    const double p[3] = {x, y, z};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      i0[d] = (int)p[d];
+      f[d] = p[d] - (double)i0[d];
+      i1[d] = i0[d] + 1 == n ? 0 : i0[d] + 1;
+    }
+    return true;
+  }
+  if (!__builtin_isfinite(x) || !__builtin_isfinite(y) || !__builtin_isfinite(z)) return false;
+  wrap_coord(x, n, i0[0], i1[0], f[0]);
+  wrap_coord(y, n, i0[1], i1[1], f[1]);
+  wrap_coord(z, n, i0[2], i1[2], f[2]);
+  return true;
+}
+
+// A weight of [0, 1] in fixed point, rounded to nearest even: w 2^40 + 2^52 is rounded to an integer by the
+// one addition, and its low 52 bits are the value (a fused multiply-add and a mask, where the conversion
+// of a double to 64 bits takes eight instructions).
+__device__ __forceinline__ unsigned long long fix_weight(double w) {
+  const double v = __builtin_fma(w, kFixScale, 4503599627370496.0);
+  return (unsigned long long)__double_as_longlong(v) & 0xfffffffffffffull;
+}
+
 // Per-axis points and weights of one coordinate for a scheme of S points (1 NGP, 2 CIC, 3 TSC).
+// i0 = floor of the wrapped coordinate, i1 the point after it, f its fraction (exact).
 template <int S>
-__device__ __forceinline__ void axis_assign(double x, int n, int (&idx)[S], double (&w)[S]) {
-  int i0, i1;
-  double f;
-  wrap_coord(x, n, i0, i1, f);  // i0 = floor of the wrapped coordinate, f its fraction (exact)
+__device__ __forceinline__ void axis_assign(int i0, int i1, double f, int n, int (&idx)[S], double (&w)[S]) {
   if constexpr (S == 2) {
     idx[0] = i0;
     idx[1] = i1;
@@ -72,16 +102,17 @@ __global__ void __launch_bounds__(256) deposit_scatter_kernel(const double* __re
                                                               double* __restrict__ bad_count) {
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < np; p += stride) {
-    const double x = pos[3 * p], y = pos[3 * p + 1], z = pos[3 * p + 2];
-    if (!__builtin_isfinite(x) || !__builtin_isfinite(y) || !__builtin_isfinite(z)) {
+    int i0[3], i1[3];
+    double f[3];
+    if (!wrap_particle(pos[3 * p], pos[3 * p + 1], pos[3 * p + 2], n, i0, i1, f)) {
       __hip_atomic_fetch_add(bad_count, 1.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       continue;
     }
     int ix[S], iy[S], iz[S];
     double wx[S], wy[S], wz[S];
-    axis_assign<S>(x, n, ix, wx);
-    axis_assign<S>(y, n, iy, wy);
-    axis_assign<S>(z, n, iz, wz);
+    axis_assign<S>(i0[0], i1[0], f[0], n, ix, wx);
+    axis_assign<S>(i0[1], i1[1], f[1], n, iy, wy);
+    axis_assign<S>(i0[2], i1[2], f[2], n, iz, wz);
 #pragma unroll
     for (int a = 0; a < S; ++a)
 #pragma unroll
@@ -90,7 +121,7 @@ __global__ void __launch_bounds__(256) deposit_scatter_kernel(const double* __re
 #pragma unroll
         for (int d = 0; d < S; ++d) {
           const double w = wx[a] * wy[b] * wz[d];
-          const unsigned long long q = (unsigned long long)__double2ull_rn(w * kFixScale);
+          const unsigned long long q = fix_weight(w);
           if (q) atomicAdd(&grid[row + iz[d]], q);
         }
       }
@@ -137,22 +168,18 @@ __global__ void __launch_bounds__(256) deposit_scatter_binned_kernel(const doubl
       p = ((ib * 2 + (lane >> 5)) * lattice + jb * 4 + ((lane >> 3) & 3)) * lattice + kb * 8 + (lane & 7);
     }
     bool valid = p < np;
-    double x = 0.0, y = 0.0, z = 0.0;
-    if (valid) {
-      x = pos[3 * p];
-      y = pos[3 * p + 1];
-      z = pos[3 * p + 2];
-      if (!__builtin_isfinite(x) || !__builtin_isfinite(y) || !__builtin_isfinite(z)) {
-        __hip_atomic_fetch_add(bad_count, 1.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        valid = false;
-      }
+    int i0[3], i1[3];
+    double f[3];
+    if (valid && !wrap_particle(pos[3 * p], pos[3 * p + 1], pos[3 * p + 2], n, i0, i1, f)) {
+      __hip_atomic_fetch_add(bad_count, 1.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      valid = false;
     }
     int ix[S], iy[S], iz[S];
     double wx[S], wy[S], wz[S];
     if (valid) {
-      axis_assign<S>(x, n, ix, wx);
-      axis_assign<S>(y, n, iy, wy);
-      axis_assign<S>(z, n, iz, wz);
+      axis_assign<S>(i0[0], i1[0], f[0], n, ix, wx);
+      axis_assign<S>(i0[1], i1[1], f[1], n, iy, wy);
+      axis_assign<S>(i0[2], i1[2], f[2], n, iz, wz);
     }
     // first point per axis before wrapping: ix[0] for CIC and NGP; for TSC ix[0] may have wrapped
     // from -1 to n - 1, which only widens the box (then the wave takes the direct path)
@@ -176,7 +203,7 @@ __global__ void __launch_bounds__(256) deposit_scatter_binned_kernel(const doubl
 #pragma unroll
             for (int d = 0; d < S; ++d) {
               const double wgt = wx[a] * wy[b] * wz[d];
-              const unsigned long long q = (unsigned long long)__double2ull_rn(wgt * kFixScale);
+              const unsigned long long q = fix_weight(wgt);
               // local coordinates from the unwrapped neighbours of the first point
               const int l = ((bx + a - lox) * ey + (by + b - loy)) * ez + (bz + d - loz);
               if (q) atomicAdd(&box[l], q);
@@ -208,7 +235,7 @@ __global__ void __launch_bounds__(256) deposit_scatter_binned_kernel(const doubl
 #pragma unroll
           for (int d = 0; d < S; ++d) {
             const double wgt = wx[a] * wy[b] * wz[d];
-            const unsigned long long q = (unsigned long long)__double2ull_rn(wgt * kFixScale);
+            const unsigned long long q = fix_weight(wgt);
             if (q) atomicAdd(&grid[row + iz[d]], q);
           }
         }
@@ -217,26 +244,37 @@ __global__ void __launch_bounds__(256) deposit_scatter_binned_kernel(const doubl
 }
 
 // ---- deposit through particles sorted by mesh tile (any particle order) ------------------------
-// The mesh is cut into tiles of 16 x 16 x 32 points. A particle belongs to the tile of the lowest
+// The mesh is cut into tiles of 16 x 16 x 32 points (4 x 16 x 32 on small meshes). A particle belongs to the tile of the lowest
 // mesh point it reaches (the first of its S points per axis, wrapped); its S^3 points then lie in
 // the tile's box of (16 + S - 1) x (16 + S - 1) x (32 + S - 1) points. Counting sort of the
-// particles by tile: count per (block of particles, tile), exclusive scan, scatter of the
+// particles by tile: count per (share of particles, tile), exclusive scan, scatter of the
 // positions into tile order. One block per tile then accumulates its particles' contributions in
 // its box in LDS (64-bit fixed point, the same rounded contribution per particle and point as the
 // scatter kernels above, so the integer sums and the result are bitwise those of the scatter) and
 // writes the whole box out; a last pass adds to every point of a tile the boxes of the (up to 7)
 // lower neighbour tiles that reach it and writes delta. No global atomics: the result does not
-// depend on particle order, and the traffic is that of reading the catalogue three times.
-constexpr int kDepTX = 16, kDepTY = 16, kDepTZ = 32;
+// depend on particle order, and the traffic is that of reading the catalogue three times and writing it
+// once, which bounds it: 256^3 particles, CIC, 484 to 499 us (604 to 619 with 256-thread blocks on contiguous ranges, a
+// division per coordinate and a conversion of eight instructions per weight), of which counting takes 95
+// (4.2 TB/s), sorting 155 (5.2 TB/s), accumulating 123 (205 with 8 wavefronts a compute unit, waiting on
+// its LDS adds) and combining 71. 96^3 points, 0.88M particles, TSC: 80 us (180), bounded by eight launches.
+constexpr int kDepTX = 16, kDepTY = 16, kDepTZ = 32;   // 4 points along x on small meshes
+constexpr int kDepNT = 1024;      // threads of the sorting and accumulating launches: two blocks fill a compute unit
+constexpr int kDepMaxBlk = 512;   // particle ranges
 
 struct DepGeom {
-  int n, tnx, tny, tnz, ntiles;
+  int n, sx, tnx, tny, tnz, ntiles, box;   // tile height 2^sx; points of a tile's box
 };
 
 template <int S>
 struct DepBox {
-  static constexpr int BX = kDepTX + S - 1, BY = kDepTY + S - 1, BZ = kDepTZ + S - 1;
-  static constexpr int CELLS = BX * BY * BZ;
+  static constexpr int BY = kDepTY + S - 1, BZ = kDepTZ + S - 1;
+  static constexpr int cells(int tx) { return (tx + S - 1) * BY * BZ; }
+  // Where point z of row r of a box of `rows` rows is stored: the tile's own 32 points of all rows, then the
+  // points past it. The tiles above in z read the latter alone, and whole lines of them.
+  __device__ static int at(int rows, int r, int z) {
+    return z < kDepTZ ? r * kDepTZ + z : rows * kDepTZ + r * (S - 1) + (z - kDepTZ);
+  }
 };
 
 // The particle's tile and its first mesh point inside the tile (false for a non-finite position).
@@ -244,29 +282,49 @@ template <int S>
 __device__ __forceinline__ bool dep_place(const double* __restrict__ pos, long long p, const DepGeom& g, int& tile,
                                           int (&ix)[S], int (&iy)[S], int (&iz)[S], double (&wx)[S], double (&wy)[S],
                                           double (&wz)[S]) {
-  const double x = pos[3 * p], y = pos[3 * p + 1], z = pos[3 * p + 2];
-  if (!__builtin_isfinite(x) || !__builtin_isfinite(y) || !__builtin_isfinite(z)) return false;
-  axis_assign<S>(x, g.n, ix, wx);
-  axis_assign<S>(y, g.n, iy, wy);
-  axis_assign<S>(z, g.n, iz, wz);
-  tile = ((ix[0] / kDepTX) * g.tny + iy[0] / kDepTY) * g.tnz + iz[0] / kDepTZ;
+  int i0[3], i1[3];
+  double f[3];
+  if (!wrap_particle(pos[3 * p], pos[3 * p + 1], pos[3 * p + 2], g.n, i0, i1, f)) return false;
+  axis_assign<S>(i0[0], i1[0], f[0], g.n, ix, wx);
+  axis_assign<S>(i0[1], i1[1], f[1], g.n, iy, wy);
+  axis_assign<S>(i0[2], i1[2], f[2], g.n, iz, wz);
+  tile = ((ix[0] >> g.sx) * g.tny + iy[0] / kDepTY) * g.tnz + iz[0] / kDepTZ;
   return true;
 }
 
-// hist[b][t]: particles of block b's range [b per, (b + 1) per) in tile t.
+// A slot for each active lane in its tile's counter. Neighbours in a lattice-ordered catalogue share a tile,
+// and LDS atomics on one address take a turn each: the lanes of the first lane's tile, then those of the
+// next one's, draw their slots with one atomic; whoever is left (another order) uses its own.
+__device__ __forceinline__ unsigned dep_slot(unsigned* __restrict__ count, int tile) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int t = __builtin_amdgcn_readfirstlane(tile);
+    if (tile == t) {
+      const unsigned long long m = __ballot(1);
+      const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+      unsigned base = 0u;
+      if (below == 0u) base = atomicAdd(&count[t], (unsigned)__popcll(m));
+      return __builtin_amdgcn_readfirstlane(base) + below;
+    }
+  }
+  return atomicAdd(&count[tile], 1u);
+}
+
+// hist[b][t]: particles of block b's share in tile t: the chunks b, b + nb, .. of kDepNT particles, so that the
+// blocks in flight read one contiguous window of the catalogue (ranges of np / nb particles start at
+// multiples of a large power of two and meet on the same memory channels).
 template <int S>
-__global__ void __launch_bounds__(256) dep_count_kernel(const double* __restrict__ pos, long long np, DepGeom g,
-                                                        long long per, unsigned* __restrict__ hist,
+__global__ void __launch_bounds__(kDepNT) dep_count_kernel(const double* __restrict__ pos, long long np, DepGeom g,
+                                                        unsigned* __restrict__ hist,
                                                         double* __restrict__ bad_count) {
   extern __shared__ unsigned dep_lds[];
   for (int t = threadIdx.x; t < g.ntiles; t += blockDim.x) dep_lds[t] = 0u;
   __syncthreads();
-  const long long p0 = (long long)blockIdx.x * per, p1 = min(np, p0 + per);
-  for (long long p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
+  for (long long p = (long long)blockIdx.x * kDepNT + threadIdx.x; p < np; p += (long long)gridDim.x * kDepNT) {
     int tile, ix[S], iy[S], iz[S];
     double wx[S], wy[S], wz[S];
     if (dep_place<S>(pos, p, g, tile, ix, iy, iz, wx, wy, wz))
-      atomicAdd(&dep_lds[tile], 1u);
+      (void)dep_slot(dep_lds, tile);
     else
       __hip_atomic_fetch_add(bad_count, 1.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -275,32 +333,38 @@ __global__ void __launch_bounds__(256) dep_count_kernel(const double* __restrict
   for (int t = threadIdx.x; t < g.ntiles; t += blockDim.x) row[t] = dep_lds[t];
 }
 
-// hist[b][t] <- particles of tile t in blocks before b; total[t]. A block takes 64 consecutive tiles
-// (one per lane, coalesced rows) and splits the blocks into 16 segments, one per wave: each wave
-// sums its segment, the segment sums are scanned in LDS, then each wave writes its prefixes.
-constexpr int kDepScanSeg = 16;
-__global__ void __launch_bounds__(64 * kDepScanSeg) dep_scan_blocks_kernel(unsigned* __restrict__ hist, int nblocks,
-                                                                           int ntiles, unsigned* __restrict__ total) {
-  __shared__ unsigned seg[kDepScanSeg][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int t = blockIdx.x * 64 + lane;
-  const int b0 = (int)(((long)w * nblocks) / kDepScanSeg), b1 = (int)(((long)(w + 1) * nblocks) / kDepScanSeg);
+// hist[b][t] <- particles of tile t in blocks before b; total[t]. A block takes 16 consecutive tiles and
+// splits the rows b into 64 segments, one per thread and tile, whose at most kDepMaxBlk / 64 counts stay in
+// registers between the sum and the prefixes: hist is read once, in loads that do not wait for each other.
+constexpr int kDepScanT = 16, kDepScanSeg = 64;
+__global__ void __launch_bounds__(kDepScanT * kDepScanSeg) dep_scan_blocks_kernel(unsigned* __restrict__ hist, int nblocks,
+                                                                                  int ntiles,
+                                                                                  unsigned* __restrict__ total) {
+  constexpr int PER = kDepMaxBlk / kDepScanSeg;
+  __shared__ unsigned seg[kDepScanSeg][kDepScanT];
+  const int tl = threadIdx.x % kDepScanT, w = threadIdx.x / kDepScanT;
+  const int t = blockIdx.x * kDepScanT + tl;
+  const int per = (nblocks + kDepScanSeg - 1) / kDepScanSeg;   // at most PER
+  unsigned v[PER];
   unsigned s = 0u;
-  if (t < ntiles)
-    for (int b = b0; b < b1; ++b) s += hist[(size_t)b * ntiles + t];
-  seg[w][lane] = s;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int b = w * per + k;
+    v[k] = k < per && b < nblocks && t < ntiles ? hist[(size_t)b * ntiles + t] : 0u;
+    s += v[k];
+  }
+  seg[w][tl] = s;
   __syncthreads();
   unsigned run = 0u;
-  for (int k = 0; k < w; ++k) run += seg[k][lane];
-  if (t < ntiles) {
-    for (int b = b0; b < b1; ++b) {
-      unsigned* c = hist + (size_t)b * ntiles + t;
-      const unsigned v = *c;
-      *c = run;
-      run += v;
-    }
-    if (w == kDepScanSeg - 1) total[t] = run;
+  for (int k = 0; k < w; ++k) run += seg[k][tl];
+  if (t >= ntiles) return;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int b = w * per + k;
+    if (k < per && b < nblocks) hist[(size_t)b * ntiles + t] = run;
+    run += v[k];
   }
+  if (w == kDepScanSeg - 1) total[t] = run;
 }
 
 // One block of 1024 threads: start[t] = particles of tiles before t, start[ntiles] = all of them.
@@ -330,20 +394,23 @@ __global__ void __launch_bounds__(1024) dep_scan_tiles_kernel(const unsigned* __
 
 // The positions of block b's particles into tile order (the order inside a tile is immaterial).
 template <int S>
-__global__ void __launch_bounds__(256) dep_scatter_kernel(const double* __restrict__ pos, long long np, DepGeom g,
-                                                          long long per, const unsigned* __restrict__ hist,
+__global__ void __launch_bounds__(kDepNT) dep_scatter_kernel(const double* __restrict__ pos, long long np, DepGeom g,
+                                                          const unsigned* __restrict__ hist,
                                                           const unsigned* __restrict__ start,
                                                           double* __restrict__ sorted) {
   extern __shared__ unsigned dep_lds[];
   const unsigned* row = hist + (size_t)blockIdx.x * g.ntiles;
   for (int t = threadIdx.x; t < g.ntiles; t += blockDim.x) dep_lds[t] = start[t] + row[t];
   __syncthreads();
-  const long long p0 = (long long)blockIdx.x * per, p1 = min(np, p0 + per);
-  for (long long p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
+  // from the end: what the counting pass read last is still in the last-level cache
+  const long long step = (long long)gridDim.x * kDepNT;
+  const long long rounds = (np + step - 1) / step;
+  for (long long p = (rounds - 1) * step + (long long)blockIdx.x * kDepNT + threadIdx.x; p >= 0; p -= step) {
+    if (p >= np) continue;
     int tile, ix[S], iy[S], iz[S];
     double wx[S], wy[S], wz[S];
     if (!dep_place<S>(pos, p, g, tile, ix, iy, iz, wx, wy, wz)) continue;
-    const unsigned slot = atomicAdd(&dep_lds[tile], 1u);
+    const unsigned slot = dep_slot(dep_lds, tile);
     double* r = sorted + 3 * (size_t)slot;
     r[0] = pos[3 * p];
     r[1] = pos[3 * p + 1];
@@ -353,21 +420,26 @@ __global__ void __launch_bounds__(256) dep_scatter_kernel(const double* __restri
 
 // One block per tile: the tile's particles into its box (LDS), the box out to boxes[tile].
 template <int S>
-__global__ void __launch_bounds__(256) dep_tile_kernel(const double* __restrict__ sorted,
+__global__ void __launch_bounds__(kDepNT) dep_tile_kernel(const double* __restrict__ sorted,
                                                        const unsigned* __restrict__ start, DepGeom g,
                                                        unsigned long long* __restrict__ boxes) {
   using B = DepBox<S>;
-  __shared__ unsigned long long box[B::CELLS];
+  extern __shared__ unsigned long long box[];
   const int t = blockIdx.x;
-  for (int c = threadIdx.x; c < B::CELLS; c += blockDim.x) box[c] = 0ull;
+  for (int c = threadIdx.x; c < g.box; c += blockDim.x) box[c] = 0ull;
   __syncthreads();
   const int tz = t % g.tnz, ty = (t / g.tnz) % g.tny, tx = t / (g.tnz * g.tny);
   const unsigned q0 = start[t], q1 = start[t + 1];
-  for (unsigned q = q0 + threadIdx.x; q < q1; q += blockDim.x) {
+  // a tile starts its share at a place of its own: those of a lattice catalogue are a power of two apart
+  const unsigned rounds = (q1 - q0 + kDepNT - 1) / kDepNT;
+  unsigned k = rounds ? (unsigned)t % rounds : 0u;
+  for (unsigned r = 0; r < rounds; ++r, k = k + 1 == rounds ? 0u : k + 1) {
+    const unsigned q = q0 + k * kDepNT + threadIdx.x;
+    if (q >= q1) continue;
     int tile, ix[S], iy[S], iz[S];
     double wx[S], wy[S], wz[S];
     (void)dep_place<S>(sorted, (long long)q, g, tile, ix, iy, iz, wx, wy, wz);   // finite by construction
-    const int lx = ix[0] - tx * kDepTX, ly = iy[0] - ty * kDepTY, lz = iz[0] - tz * kDepTZ;
+    const int lx = ix[0] - (tx << g.sx), ly = iy[0] - ty * kDepTY, lz = iz[0] - tz * kDepTZ;
 #pragma unroll
     for (int a = 0; a < S; ++a)
 #pragma unroll
@@ -375,34 +447,40 @@ __global__ void __launch_bounds__(256) dep_tile_kernel(const double* __restrict_
 #pragma unroll
         for (int d = 0; d < S; ++d) {
           const double w = wx[a] * wy[b] * wz[d];
-          const unsigned long long v = (unsigned long long)__double2ull_rn(w * kFixScale);
-          if (v) atomicAdd(&box[((lx + a) * B::BY + (ly + b)) * B::BZ + (lz + d)], v);
+          const unsigned long long v = fix_weight(w);
+          atomicAdd(&box[((lx + a) * B::BY + (ly + b)) * B::BZ + (lz + d)], v);
         }
   }
   __syncthreads();
-  unsigned long long* out = boxes + (size_t)t * B::CELLS;
-  for (int c = threadIdx.x; c < B::CELLS; c += blockDim.x) out[c] = box[c];
+  unsigned long long* out = boxes + (size_t)t * g.box;
+  const int rows = g.box / B::BZ;
+  for (int c = threadIdx.x; c < g.box; c += blockDim.x) {
+    const int x = c - rows * kDepTZ;   // in stored order: own points first
+    const int r = x < 0 ? c / kDepTZ : x / (S - 1), z = x < 0 ? c % kDepTZ : kDepTZ + x % (S - 1);
+    out[c] = box[r * B::BZ + z];
+  }
 }
 
-// One block per tile: every point of the tile sums its own box and the lower neighbours' boxes that
-// reach it; delta = count n^3 / (np 2^40) - 1; partials[tile] = the tile's sum of counts / 2^40.
+// `parts` blocks per tile: every point of the tile sums its own box and the lower neighbours' boxes that
+// reach it; delta = count n^3 / (np 2^40) - 1; partials[block] = the block's sum of counts / 2^40.
 // Writes nothing when a particle had a non-finite position (*bad_count != 0, complete since the
 // counting launch): the call then fails and leaves delta unchanged.
 template <int S>
 __global__ void __launch_bounds__(256) dep_combine_kernel(const unsigned long long* __restrict__ boxes, DepGeom g,
-                                                          double scale, double* __restrict__ delta,
+                                                          int parts, double scale, double* __restrict__ delta,
                                                           double* __restrict__ partials, const double* bad_count) {
   using B = DepBox<S>;
   __shared__ double red[16][1];
-  const int t = blockIdx.x;
+  const int t = blockIdx.x / parts, part = blockIdx.x - t * parts;
   if (*bad_count != 0.0) {
-    if (threadIdx.x == 0) partials[t] = 0.0;
+    if (threadIdx.x == 0) partials[blockIdx.x] = 0.0;
     return;
   }
   const int tz = t % g.tnz, ty = (t / g.tnz) % g.tny, tx = t / (g.tnz * g.tny);
-  const int n = g.n;
+  const int n = g.n, rows = g.box / B::BZ;
   double acc = 0.0;
-  for (int c = threadIdx.x; c < kDepTX * kDepTY * kDepTZ; c += blockDim.x) {
+  const int per = (kDepTY * kDepTZ << g.sx) / parts;
+  for (int c = part * per + threadIdx.x; c < (part + 1) * per; c += blockDim.x) {
     const int lz = c % kDepTZ, ly = (c / kDepTZ) % kDepTY, lx = c / (kDepTZ * kDepTY);
     unsigned long long v = 0ull;
 #pragma unroll
@@ -413,16 +491,16 @@ __global__ void __launch_bounds__(256) dep_combine_kernel(const unsigned long lo
       const int ny = ty - dy < 0 ? g.tny - 1 : ty - dy;
       const int nz = tz - dz < 0 ? g.tnz - 1 : tz - dz;
       const int nt = (nx * g.tny + ny) * g.tnz + nz;
-      v += boxes[(size_t)nt * B::CELLS + ((lx + dx * kDepTX) * B::BY + (ly + dy * kDepTY)) * B::BZ + (lz + dz * kDepTZ)];
+      v += boxes[(size_t)nt * g.box + B::at(rows, (lx + (dx << g.sx)) * B::BY + (ly + dy * kDepTY), lz + dz * kDepTZ)];
     }
-    const size_t cell = ((size_t)(tx * kDepTX + lx) * n + (ty * kDepTY + ly)) * n + (tz * kDepTZ + lz);
+    const size_t cell = ((size_t)((tx << g.sx) + lx) * n + (ty * kDepTY + ly)) * n + (tz * kDepTZ + lz);
     const double cnt = (double)v;
     delta[cell] = cnt * scale - 1.0;
     acc += cnt * (1.0 / kFixScale);
   }
   double vv[1] = {acc};
   block_sum<1>(vv, red, threadIdx.x, blockDim.x);
-  if (threadIdx.x == 0) partials[t] = vv[0];
+  if (threadIdx.x == 0) partials[blockIdx.x] = vv[0];
 }
 
 // delta = count * n^3 / (np * 2^40) - 1; partials[block] = the block's sum of counts / 2^40. The
@@ -469,17 +547,19 @@ static int blocks_for(size_t work, int cap) {
 template <int S>
 static int deposit_sorted(Ctx* c, const double* pos, long long np, double* delta_out) {
   const int n = c->n;
-  DepGeom g{n, n / kDepTX, n / kDepTY, n / kDepTZ, 0};
+  // Tiles of 16 points along x, of 4 where there would be fewer tiles than compute units (below 128^3): the
+  // boxes overlap more then, but every unit has one. TSC at 96^3: accumulating 34 us in 108 tiles, 20 in 432.
+  const int sx = (n / kDepTX) * (n / kDepTY) * (n / kDepTZ) < 256 ? 2 : 4;
+  DepGeom g{n, sx, n >> sx, n / kDepTY, n / kDepTZ, 0, DepBox<S>::cells(1 << sx)};
   g.ntiles = g.tnx * g.tny * g.tnz;
   const size_t cells = (size_t)n * n * n;
-  // particle ranges: at most 1024 blocks and 4M (block, tile) counters
-  int nb = (int)std::min<long long>(1024, std::max<long long>(1, (4 << 20) / g.ntiles));
-  nb = (int)std::min<long long>(nb, (np + 255) / 256);
-  const long long per = (np + nb - 1) / nb;
+  // Particle ranges: as many blocks as the chip holds at once. Longer ranges leave longer runs per tile in the
+  // sorted catalogue and fewer counters to scan.
+  const int nb = (int)std::min<long long>(kDepMaxBlk, (np + kDepNT - 1) / kDepNT);
   auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
   const size_t b_hist = al((size_t)nb * g.ntiles * 4), b_tot = al((size_t)g.ntiles * 4),
                b_start = al(((size_t)g.ntiles + 1) * 4), b_sorted = al((size_t)np * 24),
-               b_boxes = al((size_t)g.ntiles * DepBox<3>::CELLS * 8);
+               b_boxes = al((size_t)g.ntiles * DepBox<3>::cells(1 << sx) * 8);
   const size_t need = b_hist + b_tot + b_start + b_sorted + b_boxes;
   if (c->dep_bytes < need) {
     if (c->dep_mem) (void)hipFree(c->dep_mem);
@@ -498,18 +578,21 @@ static int deposit_sorted(Ctx* c, const double* pos, long long np, double* delta
   double* bad_count = c->scal + kSlotRes;
   const size_t lds = (size_t)g.ntiles * 4;
   hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, c->stream, (unsigned long long*)nullptr, (size_t)0, bad_count);
-  hipLaunchKernelGGL(dep_count_kernel<S>, dim3(nb), dim3(256), lds, c->stream, pos, np, g, per, hist, bad_count);
-  hipLaunchKernelGGL(dep_scan_blocks_kernel, dim3((g.ntiles + 63) / 64), dim3(64 * kDepScanSeg), 0, c->stream, hist, nb,
+  hipLaunchKernelGGL(dep_count_kernel<S>, dim3(nb), dim3(kDepNT), lds, c->stream, pos, np, g, hist, bad_count);
+  hipLaunchKernelGGL(dep_scan_blocks_kernel, dim3((g.ntiles + kDepScanT - 1) / kDepScanT), dim3(kDepScanT * kDepScanSeg), 0, c->stream, hist, nb,
                      g.ntiles, total);
   hipLaunchKernelGGL(dep_scan_tiles_kernel, dim3(1), dim3(1024), 0, c->stream, (const unsigned*)total, g.ntiles, start);
-  hipLaunchKernelGGL(dep_scatter_kernel<S>, dim3(nb), dim3(256), lds, c->stream, pos, np, g, per, (const unsigned*)hist,
+  hipLaunchKernelGGL(dep_scatter_kernel<S>, dim3(nb), dim3(kDepNT), lds, c->stream, pos, np, g, (const unsigned*)hist,
                      (const unsigned*)start, sorted);
-  hipLaunchKernelGGL(dep_tile_kernel<S>, dim3(g.ntiles), dim3(256), 0, c->stream, (const double*)sorted,
+  hipLaunchKernelGGL(dep_tile_kernel<S>, dim3(g.ntiles), dim3(kDepNT), (size_t)g.box * 8, c->stream, (const double*)sorted,
                      (const unsigned*)start, g, boxes);
   const double scale = (double)cells / ((double)np * kFixScale);
-  hipLaunchKernelGGL(dep_combine_kernel<S>, dim3(g.ntiles), dim3(256), 0, c->stream, (const unsigned long long*)boxes, g,
-                     scale, delta_out, c->partials, (const double*)bad_count);
-  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, c->stream, (const double*)c->partials, g.ntiles,
+  // four blocks a tile where tiles are few (TSC at 96^3 31 -> 10 us); at 256^3 they cost more than they
+  // give (86 us against 77)
+  const int parts = g.ntiles <= 512 ? 4 : 1;
+  hipLaunchKernelGGL(dep_combine_kernel<S>, dim3(g.ntiles * parts), dim3(256), 0, c->stream,
+                     (const unsigned long long*)boxes, g, parts, scale, delta_out, c->partials, (const double*)bad_count);
+  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, c->stream, (const double*)c->partials, g.ntiles * parts,
                      c->scal + kSlotRes + 1);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "mr_deposit");
@@ -622,17 +705,15 @@ __global__ void __launch_bounds__(256) lag_gather_kernel(const double* __restric
   // consecutive particles on one XCD: lattice-ordered catalogues then reuse mesh lines in its L2
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long p = xcd_remap(blockIdx.x, gridDim.x) * (long long)blockDim.x + threadIdx.x; p < np; p += stride) {
-    const double x = pos[3 * p], y = pos[3 * p + 1], z = pos[3 * p + 2];
-    if (!__builtin_isfinite(x) || !__builtin_isfinite(y) || !__builtin_isfinite(z)) {
+    int i0[3], i1[3];
+    double f[3];
+    if (!wrap_particle(pos[3 * p], pos[3 * p + 1], pos[3 * p + 2], n, i0, i1, f)) {
       __hip_atomic_fetch_add(bad_count, 1.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       disp[3 * p] = disp[3 * p + 1] = disp[3 * p + 2] = __builtin_nan("");
       continue;
     }
-    int ix0, ix1, iy0, iy1, iz0, iz1;
-    double fx, fy, fz;
-    wrap_coord(x, n, ix0, ix1, fx);
-    wrap_coord(y, n, iy0, iy1, fy);
-    wrap_coord(z, n, iz0, iz1, fz);
+    const int ix0 = i0[0], ix1 = i1[0], iy0 = i0[1], iy1 = i1[1], iz0 = i0[2], iz1 = i1[2];
+    const double fx = f[0], fy = f[1], fz = f[2];
     const double wx[2] = {1.0 - fx, fx}, wy[2] = {1.0 - fy, fy}, wz[2] = {1.0 - fz, fz};
     const int ix[2] = {ix0, ix1}, iy[2] = {iy0, iy1}, iz[2] = {iz0, iz1};
     // all 24 loads are issued before the first use so that their latencies overlap
@@ -671,17 +752,15 @@ __global__ void __launch_bounds__(256) lag_gather_theta_kernel(const double* __r
                                                               double* __restrict__ bad_count) {
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long p = xcd_remap(blockIdx.x, gridDim.x) * (long long)blockDim.x + threadIdx.x; p < np; p += stride) {
-    const double x = pos[3 * p], y = pos[3 * p + 1], z = pos[3 * p + 2];
-    if (!__builtin_isfinite(x) || !__builtin_isfinite(y) || !__builtin_isfinite(z)) {
+    int i0[3], i1[3];
+    double f[3];
+    if (!wrap_particle(pos[3 * p], pos[3 * p + 1], pos[3 * p + 2], n, i0, i1, f)) {
       __hip_atomic_fetch_add(bad_count, 1.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       disp[3 * p] = disp[3 * p + 1] = disp[3 * p + 2] = __builtin_nan("");
       continue;
     }
-    int ix0, ix1, iy0, iy1, iz0, iz1;
-    double fx, fy, fz;
-    wrap_coord(x, n, ix0, ix1, fx);
-    wrap_coord(y, n, iy0, iy1, fy);
-    wrap_coord(z, n, iz0, iz1, fz);
+    const int ix0 = i0[0], ix1 = i1[0], iy0 = i0[1], iy1 = i1[1], iz0 = i0[2], iz1 = i1[2];
+    const double fx = f[0], fy = f[1], fz = f[2];
     const int xm = ix0 == 0 ? n - 1 : ix0 - 1, xp = ix1 == n - 1 ? 0 : ix1 + 1;
     const int ym = iy0 == 0 ? n - 1 : iy0 - 1, yp = iy1 == n - 1 ? 0 : iy1 + 1;
     const int zm = iz0 == 0 ? n - 1 : iz0 - 1, zp = iz1 == n - 1 ? 0 : iz1 + 1;

@@ -777,12 +777,14 @@ int Ctx::adj_blk_cycle(int l, double* r2) {
   int rc;
   if (r2) {
     double p[kBlkMaxBlocks];
-    if ((rc = read_device(d.part_r2, nb, p)) != MR_OK) return rc;
+    if ((rc = read_begin(d.part_r2, nb)) != MR_OK) return rc;
+    if (adj_ahead && (rc = adj_blk_cycle(l + 1, nullptr)) != MR_OK) return rc;
+    if ((rc = read_end(nb, p)) != MR_OK) return rc;
     *r2 = 0.0;
     for (int b = 0; b < nb; ++b) *r2 += p[b];
     if (std::sqrt(*r2) <= adj_stop) return MR_OK;
   }
-  if ((rc = adj_blk_cycle(l + 1, nullptr)) != MR_OK) return rc;
+  if (!(r2 && adj_ahead) && (rc = adj_blk_cycle(l + 1, nullptr)) != MR_OK) return rc;
   AdjUpArgs u{};
   u.lam = A.lam[A.cur];
   u.rhs = A.rhs;
@@ -917,12 +919,14 @@ int Ctx::adjoint_solve(const double* delta, const double* theta_star, const doub
   if (r0 == 0.0) r0 = 1.0;
   adj_stop = opts.tol * r0;
   int cyc = 0, status = MR_OK;
-  double rel = (loc.r0_norm == 0.0) ? 0.0 : 1.0;
+  double rel = (loc.r0_norm == 0.0) ? 0.0 : 1.0, prev = rel;
   while (rel > opts.tol && cyc < opts.max_cycles) {
     if (aa_depth > 0 && aa.steps == 0 && (e = aa_save(*this, A0.lam[A0.cur])) != hipSuccess)
       return hip_fail(e, "Anderson save");
+    adj_ahead = run_ahead(rel, prev, opts.tol) && cyc + 1 < opts.max_cycles;
     if ((rc = adj_vcycle(0, scal + kSlotAux + 6)) != MR_OK) return rc;
     ++cyc;
+    prev = rel;
     rel = adj_last_norm / r0;
     if (cyc < 128) loc.history[cyc] = rel;
     if (!std::isfinite(rel)) {

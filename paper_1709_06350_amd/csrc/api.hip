@@ -133,9 +133,19 @@ Reduce Ctx::reducer(int slot) { return Reduce{partials, counter, scal + slot}; }
 int Ctx::read_scalars(int slot, int count, double* out) { return read_device(scal + slot, count, out); }
 
 int Ctx::read_device(const double* from, int count, double* out) {
+  const int rc = read_begin(from, count);
+  return rc == MR_OK ? read_end(count, out) : rc;
+}
+
+int Ctx::read_begin(const double* from, int count) {
   if (count > kHostSlots) return fail(MR_EINVAL, "read back: too many values");
   hipError_t e = hipMemcpyAsync(host, from, count * sizeof(double), hipMemcpyDeviceToHost, stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  if (e == hipSuccess) e = hipEventRecord(host_ready, stream);
+  return e == hipSuccess ? MR_OK : hip_fail(e, "read back");
+}
+
+int Ctx::read_end(int count, double* out) {
+  const hipError_t e = hipEventSynchronize(host_ready);
   if (e != hipSuccess) return hip_fail(e, "read back");
   for (int i = 0; i < count; ++i) out[i] = host[i];
   return MR_OK;
@@ -546,7 +556,7 @@ int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_de
   loc.history[0] = rel;
   int cyc = 0;
   int status = MR_OK;
-  double best = rel;
+  double best = rel, prev = rel;
   const bool blk0 = blk_first() == 0;
   L0.cp = lsum(0);
   L0.cp_count = 2;
@@ -558,11 +568,15 @@ int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_de
       if (e != hipSuccess) return hip_fail(e, "Anderson save");
     }
     double shift, sd = 0.0, sd2 = 0.0;   // C, sum d and sum d^2 of the defect pass
+    bool ahead = false;                  // the coarse part of this cycle is enqueued already
     if (blk0) {
       const int nb = blk_blocks(L0.n);
       if ((rc = blk_down(0, L0.cp, L0.cp_count, 1.0 / N3)) != MR_OK) return rc;
       std::vector<double> r(2 * nb + 1);
-      if ((rc = read_device(part_d(L0), 2 * nb + 1, r.data())) != MR_OK) return rc;
+      if ((rc = read_begin(part_d(L0), 2 * nb + 1)) != MR_OK) return rc;
+      ahead = run_ahead(rel, prev, opts.tol) && cyc + 1 < opts.max_cycles;
+      if (ahead && (rc = blk_cycle(1, part_d(L0), nb, -1.0 / N3)) != MR_OK) return rc;
+      if ((rc = read_end(2 * nb + 1, r.data())) != MR_OK) return rc;
       for (int b = 0; b < nb; ++b) {
         sd += r[b];
         sd2 += r[nb + b];
@@ -579,6 +593,7 @@ int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_de
     const double var = sd2 - sd * sd / N3;
     nrm = std::sqrt(var > 0.0 ? var : 0.0);
     msig = shift - sd / N3;
+    prev = rel;
     rel = nrm / r0;
     ++cyc;
     if (cyc < 128) loc.history[cyc] = rel;
@@ -589,7 +604,7 @@ int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_de
     if (rel < best) best = rel;
     if (rel <= opts.tol || cyc >= opts.max_cycles) break;
     if (blk0) {
-      rc = blk_cycle(1, part_d(L0), blk_blocks(L0.n), -1.0 / N3);
+      rc = ahead ? MR_OK : blk_cycle(1, part_d(L0), blk_blocks(L0.n), -1.0 / N3);
       if (rc == MR_OK) rc = blk_up(0);
     } else {
       rc = up(0, scal + kSlotRes);
@@ -711,6 +726,7 @@ int mr_create(mr_ctx** out, int n, const mr_opts* opts, void* hip_stream) {
   if (e == hipSuccess) e = hipMemset(c->counter, 0, 64 * sizeof(unsigned));
   if (e == hipSuccess) e = hipMemset(c->scal, 0, kSlotCount * sizeof(double));
   if (e == hipSuccess) e = hipHostMalloc((void**)&c->host, kHostSlots * sizeof(double), hipHostMallocDefault);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->host_ready, hipEventDisableTiming);
   if (e != hipSuccess) {
     rc = hip_fail(e, "mr_create");
     mr_destroy(reinterpret_cast<mr_ctx*>(c));
@@ -768,6 +784,7 @@ void mr_destroy(mr_ctx* h) {
   c->timer.destroy();
   for (void* p : c->owned) (void)hipFree(p);
   if (c->host) (void)hipHostFree(c->host);
+  if (c->host_ready) (void)hipEventDestroy(c->host_ready);
   delete c;
 }
 

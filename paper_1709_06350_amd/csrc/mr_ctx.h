@@ -28,6 +28,16 @@ constexpr int kSlotTmax = 114;   // max |theta| (as the bits of a non-negative d
 constexpr int kSlotCount = 128;
 constexpr int kHostSlots = 1040;   // host copies of scalars, or of the block sums of a finest mesh in the block form
 
+// On meshes whose finest level runs in the block form the residual norm of a cycle takes about as long to
+// reach the host as a launch runs, and the chip would wait for the host's next launch. The coarse part of
+// the cycle reads and writes coarser levels only, so it is enqueued before the norm is known, unless the
+// contraction of the last cycle puts this one's residual below twice the tolerance: it is then likely the
+// last, and its coarse part would be for nothing. Solve and gradient at 64^3
+// 4.09 -> 3.76 ms, solve at 32^3 0.99 -> 0.97.
+inline bool run_ahead(double rel, double prev, double tol) {
+  return rel * (rel < prev ? rel / prev : 1.0) > 2.0 * tol;
+}
+
 // One mesh of the hierarchy. All fields colour-split; th[0], th[1] are the ping-pong buffers
 // (both colours each), th[cur] the current iterate.
 struct Level {
@@ -91,6 +101,7 @@ struct Ctx {
   double* partials = nullptr;
   unsigned int* counter = nullptr;
   double* host = nullptr;
+  hipEvent_t host_ready = nullptr;   // the last copy into host (read_begin)
   std::vector<void*> owned;
   EventTimer timer;
   unsigned long long* cic_grid = nullptr;   // fixed-point CIC accumulation grid (allocated on first use)
@@ -105,6 +116,8 @@ struct Ctx {
   Reduce reducer(int slot);
   int read_scalars(int slot, int count, double* out);
   int read_device(const double* from, int count, double* out);
+  int read_begin(const double* from, int count);   // the copy alone; what is enqueued next runs while
+  int read_end(int count, double* out);            // read_end waits for it
   int write_scalars(int slot, double v0, double v1, int count = 2);
   double* lsum(int l) { return scal + kSlotLevel + 3 * l; }
   int sweep(int l);
@@ -132,6 +145,7 @@ struct Ctx {
   int adj_blk_cycle(int l, double* r2);
   bool tail_form(int t) const;
   double adj_last_norm = 0.0, adj_stop = 0.0;
+  bool adj_ahead = false;   // the next cycle of the adjoint is expected not to be the last
   double* linsum(int l);
   int lin_sweep(int l, bool zero_start = false);
   int lin_vcycle(int l, bool zero = false);

@@ -751,8 +751,8 @@ __global__ void __launch_bounds__(256) lag_gather_kernel(const double* __restric
 // beside them 2. They are read in pairs, 16 loads of 16 bytes; only a particle in the first or one of the
 // last two cells of a row needs the single points across the seam. OFF: byte offsets in 32 bits, where
 // the mesh has less than 4 GiB, go into the load as they are; 64 bits beyond. 256^3 particles on 256^3:
-// 374 us, 2.5 TB/s of compulsory bytes (456 with 32 loads of 8 bytes): the first-level caches deliver 16
-// KB a wavefront. Slower: blocks of 1024 (402), blocks that stay and fetch the next position (421).
+// 374 us, 2.5 TB/s of compulsory bytes (456 with 32 loads of 8 bytes), so the gathered loads, 16 KB a
+// wavefront, bound it and not memory. Slower: blocks of 1024 (402), blocks that stay and fetch the next position (421).
 struct __attribute__((packed, aligned(8))) LagPair {
   double a, b;
 };

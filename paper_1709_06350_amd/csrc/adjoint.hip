@@ -777,9 +777,14 @@ int Ctx::adj_blk_cycle(int l, double* r2) {
   int rc;
   if (r2) {
     double p[kBlkMaxBlocks];
-    if ((rc = read_begin(d.part_r2, nb)) != MR_OK) return rc;
-    if (adj_ahead && (rc = adj_blk_cycle(l + 1, nullptr)) != MR_OK) return rc;
-    if ((rc = read_end(nb, p)) != MR_OK) return rc;
+    if (adj_ahead) {
+      if ((rc = read_begin(d.part_r2, nb)) != MR_OK) return rc;
+      if ((rc = adj_blk_cycle(l + 1, nullptr)) != MR_OK) return rc;
+      rc = read_end(nb, p);
+    } else {
+      rc = read_device(d.part_r2, nb, p);
+    }
+    if (rc != MR_OK) return rc;
     *r2 = 0.0;
     for (int b = 0; b < nb; ++b) *r2 += p[b];
     if (std::sqrt(*r2) <= adj_stop) return MR_OK;

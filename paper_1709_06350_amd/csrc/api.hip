@@ -133,8 +133,12 @@ Reduce Ctx::reducer(int slot) { return Reduce{partials, counter, scal + slot}; }
 int Ctx::read_scalars(int slot, int count, double* out) { return read_device(scal + slot, count, out); }
 
 int Ctx::read_device(const double* from, int count, double* out) {
-  const int rc = read_begin(from, count);
-  return rc == MR_OK ? read_end(count, out) : rc;
+  if (count > kHostSlots) return fail(MR_EINVAL, "read back: too many values");
+  hipError_t e = hipMemcpyAsync(host, from, count * sizeof(double), hipMemcpyDeviceToHost, stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  if (e != hipSuccess) return hip_fail(e, "read back");
+  for (int i = 0; i < count; ++i) out[i] = host[i];
+  return MR_OK;
 }
 
 int Ctx::read_begin(const double* from, int count) {
@@ -573,10 +577,15 @@ int Ctx::solve_fp64(const double* delta, double* theta, mr_info* info, int aa_de
       const int nb = blk_blocks(L0.n);
       if ((rc = blk_down(0, L0.cp, L0.cp_count, 1.0 / N3)) != MR_OK) return rc;
       std::vector<double> r(2 * nb + 1);
-      if ((rc = read_begin(part_d(L0), 2 * nb + 1)) != MR_OK) return rc;
       ahead = run_ahead(rel, prev, opts.tol) && cyc + 1 < opts.max_cycles;
-      if (ahead && (rc = blk_cycle(1, part_d(L0), nb, -1.0 / N3)) != MR_OK) return rc;
-      if ((rc = read_end(2 * nb + 1, r.data())) != MR_OK) return rc;
+      if (ahead) {
+        if ((rc = read_begin(part_d(L0), 2 * nb + 1)) != MR_OK) return rc;
+        if ((rc = blk_cycle(1, part_d(L0), nb, -1.0 / N3)) != MR_OK) return rc;
+        rc = read_end(2 * nb + 1, r.data());
+      } else {
+        rc = read_device(part_d(L0), 2 * nb + 1, r.data());
+      }
+      if (rc != MR_OK) return rc;
       for (int b = 0; b < nb; ++b) {
         sd += r[b];
         sd2 += r[nb + b];

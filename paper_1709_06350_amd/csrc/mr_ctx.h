@@ -116,8 +116,10 @@ struct Ctx {
   Reduce reducer(int slot);
   int read_scalars(int slot, int count, double* out);
   int read_device(const double* from, int count, double* out);
-  int read_begin(const double* from, int count);   // the copy alone; what is enqueued next runs while
-  int read_end(int count, double* out);            // read_end waits for it
+  // The copy alone; what is enqueued next runs while read_end waits for it. Only for that: the event costs more
+  // than the stream's wait (a deposit with two read-backs and nothing behind them 65 to 75 us against 40).
+  int read_begin(const double* from, int count);
+  int read_end(int count, double* out);
   int write_scalars(int slot, double v0, double v1, int count = 2);
   double* lsum(int l) { return scal + kSlotLevel + 3 * l; }
   int sweep(int l);

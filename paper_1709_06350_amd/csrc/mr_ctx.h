@@ -33,7 +33,7 @@ constexpr int kHostSlots = 1040;   // host copies of scalars, or of the block su
 // the cycle reads and writes coarser levels only, so it is enqueued before the norm is known, unless the
 // contraction of the last cycle puts this one's residual below twice the tolerance: it is then likely the
 // last, and its coarse part would be for nothing. Solve and gradient at 64^3
-// 4.09 -> 3.76 ms, solve at 32^3 0.99 -> 0.97.
+// 4.09 -> 3.76..3.86 ms, solve at 32^3 0.99 -> 0.91.
 inline bool run_ahead(double rel, double prev, double tol) {
   return rel * (rel < prev ? rel / prev : 1.0) > 2.0 * tol;
 }

@@ -188,9 +188,9 @@ int mr_get_lin_schedule(mr_ctx* ctx, int level, int sched[4]);
  * unsigned 64-bit fixed point (each weight rounded to a multiple of 2^-40 of a particle's mass
  * before the sum), so the result is bitwise reproducible and independent of the particles' order.
  * CIC and TSC on meshes with n a multiple of 32 up to 512 first sort the particles by mesh tile
- * (16 x 16 x 32 points, 4 x 16 x 32 below 128^3; counting sort on the device) and accumulate each tile in LDS, without global
- * atomics; this needs 24 bytes per particle and 11 to 15 bytes per mesh point of device memory,
- * kept with the context. NGP, other meshes and MR_FLAG_DEPOSIT_SCATTER use atomic scatter kernels
+ * (16 x 16 x 32 points, 4 x 16 x 32 below 128^3; counting sort on the device) and accumulate each tile
+ * in LDS, without global atomics; this needs 24 bytes per particle and 11 to 15 bytes per mesh point of
+ * device memory, kept with the context. NGP, other meshes and MR_FLAG_DEPOSIT_SCATTER use atomic scatter kernels
  * into a 64-bit grid; both ways give the same result bit for bit. Returns MR_EINVAL for a NULL argument,
  * np < 1, a mass that is not positive and finite, an unknown scheme, or particles with a
  * non-finite coordinate (then delta_out is left unchanged); a cell can hold at most 2^24

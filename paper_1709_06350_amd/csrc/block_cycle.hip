@@ -324,7 +324,7 @@ struct TailLevel {
       for (int c = 0; c < 2; ++c) {
         double sig[PER], S[PER];
         source(c, sig, S);
-        if (!WAVE) tail_sync<WAVE>();
+        tail_sync<WAVE>();   // every lane has read its neighbours before any of them is overwritten
 #pragma unroll
         for (int p = 0; p < PER; ++p)
           if (has[p]) {

@@ -274,8 +274,8 @@ int mr_adjoint_solve_anderson(mr_ctx* ctx, const double* delta, const double* th
 
 /* Batched solve of nbox independent periodic boxes of possibly different sizes (the one-mesh
  * solve applied box by box, Sec. II.A, in the mixed-precision form). n: host array of nbox box
- * sizes (each even, 8..1024, coarsest level at most 12^3). delta, theta: host arrays of nbox
- * device pointers, delta[b] and theta[b] of n[b]^3 doubles in natural order; theta[b] is
+ * sizes (4 2^k or 6 2^k cells a side, 8..1024: 8, 12, 16, 24, 32, ...; others are refused). delta,
+ * theta: host arrays of nbox device pointers, delta[b] and theta[b] of n[b]^3 doubles in natural order; theta[b] is
  * written (zero mean), every box starts from theta = 0. opts: as for mr_create (NULL: the
  * defaults); precision and warm_start are ignored. Each phase of an outer iteration is one
  * launch per distinct box size covering all boxes of that size; one outer iteration is captured

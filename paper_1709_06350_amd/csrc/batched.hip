@@ -491,8 +491,8 @@ __global__ void __launch_bounds__(256) b_aa_combine_kernel(const BBox* boxes, co
 
 // ---- FP32 sweep tile tuner ----------------------------------------------------------------
 
-#define MR_BLIN_TILES(X) X(48, 16) X(48, 8) X(40, 16) X(40, 8) X(64, 16) X(64, 8) X(64, 4) X(32, 8) X(16, 16) X(8, 16) X(4, 8) X(2, 4)
-#define MR_BRT_TILES(X) X(48, 8) X(40, 8) X(64, 8) X(32, 8) X(16, 8) X(8, 8) X(4, 8)
+#define MR_BLIN_TILES(X) X(48, 16) X(48, 8) X(64, 16) X(64, 8) X(64, 4) X(32, 8) X(16, 16) X(8, 16) X(4, 8) X(2, 4)
+#define MR_BRT_TILES(X) X(48, 8) X(64, 8) X(32, 8) X(16, 8) X(8, 8) X(4, 8)
 
 static hipError_t launch_b_lin_sweep(const BBox* boxes, const int* cls, int nb, const TileCfg& t, int l, int colour, int cur,
                                      int n, double h, hipStream_t s, bool zero_black = false) {
@@ -522,7 +522,7 @@ static hipError_t launch_b_lin_sweep(const BBox* boxes, const int* cls, int nb, 
 static std::vector<TileCfg> lin_candidates(int n) {
   std::vector<TileCfg> out;
   const int nh = n / 2;
-  static const int shapes[][2] = {{48, 16}, {48, 8}, {40, 16}, {40, 8}, {64, 16}, {64, 8}, {64, 4}, {32, 8}, {16, 16}, {8, 16}, {4, 8}, {2, 4}};
+  static const int shapes[][2] = {{48, 16}, {48, 8}, {64, 16}, {64, 8}, {64, 4}, {32, 8}, {16, 16}, {8, 16}, {4, 8}, {2, 4}};
   auto fits = [&](const int* sh) { return nh % sh[0] == 0 && sh[0] <= nh && n % sh[1] == 0 && sh[1] <= n; };
   bool big = false;
   for (const auto& sh : shapes) big = big || (fits(sh) && sh[0] * sh[1] >= 128);
@@ -709,7 +709,7 @@ struct SizeClass {
 // units of 4 planes, chunks of at least 8 planes) that gives each box about 64 blocks. It depends on
 // n only, so a box is reduced in the same order whatever else is in the batch.
 BTile pick_btile(int n) {
-  static const int pref[][2] = {{64, 8}, {48, 8}, {40, 8}, {32, 8}, {16, 8}, {8, 8}, {4, 8}};
+  static const int pref[][2] = {{64, 8}, {48, 8}, {32, 8}, {16, 8}, {8, 8}, {4, 8}};
   BTile t;
   if (n % 8 != 0) return t;
   for (const auto& p : pref) {
@@ -766,10 +766,11 @@ int rows_grid_b(int rows) { return rows < 1024 ? rows : 1024; }
 // chip together, so the tiles are the larger ones, whose halo is a smaller share of the work. At 48^3
 // down and up of 21 boxes take 228 us (the plain launches about 320). At 64^3 the two sides meet: a batch
 // of 64 boxes of 64^3-128^3 takes 133.0 ms with the form at 64^3 and 127.2 without, 8 boxes 31.5 and 39.1,
-// 2 boxes 11.4 and 15.8; the form ends there.
+// 2 boxes 11.4 and 15.8; the form ends there. Batches take boxes of 4 2^k and 6 2^k cells a side (the FP32
+// sweep has no tile and chunk for the 20^3 mesh of the others), so these are all the levels there are.
 static BlkTile batch_blk_tile(int n) {
   if (n == 64) return BlkTile{8, 8, 16};
-  if (n >= 24 && n <= 48 && n % 8 == 0) return BlkTile{8, 8, 8};
+  if (n == 24 || n == 32 || n == 48) return BlkTile{8, 8, 8};
   if (n == 16) return BlkTile{4, 4, 8};
   return BlkTile{0, 0, 0};
 }

@@ -251,7 +251,7 @@ __global__ void __launch_bounds__(NT) adj_up_kernel(AdjUpArgs a) {
 // with a one-cell periodic halo, rhs in the registers of the cell's owner, the coefficients in LDS (the
 // smaller meshes) or read from memory (12^3). The mean is taken out after every sweep (as an offset
 // that the next reads subtract). The coarsest mesh is swept by one wavefront.
-template <int N, bool WAVE, int W, bool LDSC>
+template <int N, bool WAVE, int W>
 struct AdjTailLevel {
   using B = Box<N, N, N, 1>;
   static constexpr int HALF = N * N * N / 2, PER = (HALF + W - 1) / W;
@@ -359,8 +359,8 @@ struct AdjTailLevel {
 template <int NA, int NB, int NT>
 __global__ void __launch_bounds__(NT) adj_tail_kernel(AdjTailArgs a) {
   constexpr bool LDSA = NA <= 8;
-  using LA = AdjTailLevel<NA, false, NT, LDSA>;
-  using LB = AdjTailLevel<NB == 0 ? 4 : NB, true, 64, true>;
+  using LA = AdjTailLevel<NA, false, NT>;
+  using LB = AdjTailLevel<NB == 0 ? 4 : NB, true, 64>;
   constexpr int CA = NA * NA * NA, CB = NB == 0 ? 1 : NB * NB * NB;
   __shared__ double lamA[2 * LA::B::HALF], rA[NB == 0 ? 1 : CA], cA[LDSA ? 6 * CA : 1];
   __shared__ double lamB[2 * LB::B::HALF], cB[6 * CB], ec[NB == 0 ? 1 : (NB + 2) * (NB + 2) * (NB + 2)];

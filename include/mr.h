@@ -73,7 +73,10 @@ typedef struct {
 /* MR_FLAG_EAGER (mr_solve_batched only): launch every pass directly on the stream instead of
  * replaying the captured graph (same kernels and arguments; for checking the graph against direct
  * launches). MR_FLAG_TWO_PASS: relax with one launch per colour (red, then black from the new
- * red values) instead of the fused red-black launch; both compute the same update.
+ * red values) instead of the fused red-black launch; both compute the same update. It also switches the block
+ * form of small levels off (mr_set_schedule below; FP64 and mixed solves), which refreshes the uniform
+ * shift once per launch instead of once per sweep: the same solution, but iterates and, by a few, cycle counts
+ * differ. MR_FLAG_ORDER4 (FP64) and MR_FLAG_ADJ_ROWS / MR_FLAG_ADJ_TILED (adjoint) switch it off too.
  * MR_FLAG_ADJ_ROWS / MR_FLAG_ADJ_TILED (mr_adjoint_solve): relax the adjoint with the untiled
  * row kernel on every level, or with the tiled plane-marching kernel on every level a compiled
  * tile fits, instead of the per-level timed choice; all compute the same update up to rounding
@@ -151,7 +154,8 @@ int mr_levels(const mr_ctx* ctx);
  * a level pinned with mr_set_schedule, every level above it, and the finest level while
  * mr_timing_enable is on run sweeps on their schedules. For callers that need the schedule
  * the solve ran (reports, profiling of one configuration) or identical schedules in several
- * processes (bitwise-equal results): mr_get_schedule reads it, mr_set_schedule pins it (not a
+ * processes (bitwise-equal results): mr_get_schedule reads it, mr_set_schedule pins it (in every process,
+ * the one it was read in too: a level that is not pinned may run the block form; not a
  * passage of the paper). Host-only, no device work. Returns MR_EINVAL for a NULL argument, a level
  * out of range, or a schedule the library has no kernel for (set: the tile must be compiled and
  * divide the level's mesh, chunks must hold at least 4 planes each (MR_SCHED_FUSED splits the

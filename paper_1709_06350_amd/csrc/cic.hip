@@ -259,7 +259,9 @@ __global__ void __launch_bounds__(256) deposit_scatter_binned_kernel(const doubl
 // (4.2 TB/s), sorting 155 (5.2 TB/s), accumulating 123 (205 with 8 wavefronts a compute unit, waiting on
 // its LDS adds) and combining 71. 96^3 points, 0.88M particles, TSC: 80 us (180), bounded by eight launches.
 constexpr int kDepTX = 16, kDepTY = 16, kDepTZ = 32;   // 4 points along x on small meshes
-constexpr int kDepNT = 1024;      // threads of the sorting and accumulating launches: two blocks fill a compute unit
+// Threads of the sorting and accumulating launches: two blocks fill a compute unit, except where a TSC box of a
+// 16 x 16 x 32 tile takes 88 KB of LDS and one block has it to itself.
+constexpr int kDepNT = 1024;
 constexpr int kDepMaxBlk = 512;   // particle ranges
 
 struct DepGeom {
